@@ -23,6 +23,12 @@ extern "C" __global__ void fv_small_flash32_kernel(const EngineArgs* __restrict_
 extern "C" __global__ void fv_small_flash64_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_small_flash128_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_small_flash256_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_bound1k_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_team1k_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_team4k_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_team16k_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_colmax_kernel(const float* __restrict__ log_a, int32_t K, uint32_t* __restrict__ cmax,
+                                            uint4* __restrict__ zero, int64_t nzero);
 extern "C" __global__ void fv_fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v);
 extern "C" __global__ void fv_validate_array_kernel(const float* __restrict__ p, int64_t n, int32_t* __restrict__ flag);
 extern "C" __global__ void fv_validate_points_kernel(const double* __restrict__ p, int64_t n, int32_t* flag);
@@ -34,7 +40,8 @@ extern "C" __global__ void fv_model_check_kernel(const fv_seq* seqs_dev, int32_t
                                                  int32_t* status);
 extern "C" __global__ void fv_prep_dense_kernel(const float* __restrict__ log_a, int32_t K, int32_t Kp,
                                                 float* __restrict__ Ap);
-extern "C" __global__ void fv_transpose_dense_kernel(const float* __restrict__ Ap, int32_t Kp, float* __restrict__ At);
+extern "C" __global__ void fv_transpose_dense_kernel(const float* __restrict__ Ap, int32_t Kp, float* __restrict__ At,
+                                                     const int32_t* __restrict__ need);
 extern "C" __global__ void fv_setup_kernel(EngineArgs a, SetupArgs sa);
 extern "C" __global__ void fv_finish_kernel(EngineArgs a, int32_t* status);
 extern "C" __global__ void fv_beam_finish_kernel(EngineArgs a, const float* __restrict__ Ap, int32_t* status);
@@ -110,6 +117,8 @@ constexpr int32_t kMaxSparseK = 1 << 30;
 constexpr int64_t kMaxNnz = 0x7fffffffLL;
 constexpr int32_t kMaxBlocks = 4096;    // engine grid size limit (arrival flags)
 constexpr int kEngineBlock = 1024;      // engine threads per block (one block per CU)
+constexpr int kTeamBlock = 1024;        // threads per block of a team,
+constexpr int kBoundBlock = 1024;       // of a single block's task
 
 struct Region {
     size_t off = 0, bytes = 0;
@@ -130,6 +139,11 @@ struct DenseLayout {
     int64_t div_off = 0;         // their offset in a slot, in floats
     int32_t leaf_len = 0;        // the longest leaf that can occur (table rows per slot)
     int64_t leaf_off = 0;        // its offset in a slot, in floats
+    int32_t max_seg = 0;         // longest first-level FLASH segment, in positions
+    int64_t n_segs = 0;          // first-level FLASH segments of at least two positions
+    int32_t team = 0, teams = 0; // bounded decodes: blocks of a team, and teams (0: not bounded)
+    int64_t xch_bytes = 0;       // a team's exchange buffer
+    Region cmax, xch;            // column maxima and exchange buffers of bounded decodes
     int64_t leaf_tasks = 0;      // task-tree nodes when leaves end the bisection (slot sizing)
     Region Ap, At, seq1, seqinfo, keys, args, state, arrive, rows_full, rows_light, rows_beam, queue, free_stack,
         slots, alpha, root, psi, csr_flag, csr_ptr, csr_deg, csr_eid, csr_src, csr_val;
@@ -203,11 +217,12 @@ fv_status plan_dense(int32_t method, const fv_trans* A, const int32_t* T_host, i
     L.K = K;
     L.Kp = (int32_t)round_up(K, kKAlign);
     L.n_seqs = n_seqs;
-    int64_t nonempty = 0;
+    int64_t nonempty = 0, max_T = 0;
     for (int32_t b = 0; b < n_seqs; ++b) {
         const int32_t T = T_host[b];
         if (T < 0) return fail(FV_E_INVALID_ARG, "sequence %d has negative length %d", b, T);
         L.sum_T += T;
+        max_T = std::max<int64_t>(max_T, T);
         if (T == 0) continue;
         ++nonempty;
         if (method == FV_VANILLA) {
@@ -216,6 +231,8 @@ fv_status plan_dense(int32_t method, const fv_trans* A, const int32_t* T_host, i
         } else {
             const int32_t pp = eff_parallelism(T, P);
             L.sum_root += (beam ? 1 : 2) * (int64_t)(pp - 1);
+            L.max_seg = std::max(L.max_seg, (T + pp - 1) / pp);
+            L.n_segs += T > pp ? std::min(pp, T - pp) : 0;
             L.n_tasks += T - pp + 1;
         }
     }
@@ -290,6 +307,27 @@ fv_status plan_dense(int32_t method, const fv_trans* A, const int32_t* T_host, i
     put(cur, L.Ap, (!sparse && L.Kp != K) ? (size_t)L.Kp * L.Kp * 4 : 0);  // padded dense copy only when needed
     // transposed copy for the two-column items of moderate K
     put(cur, L.At, (!sparse && L.Kp <= kColMaxKp) ? (size_t)L.Kp * L.Kp * 4 : 0);
+    if (!sparse && !beam && K <= kBoundMaxK) {
+        // a block owns up to kTeamGroups groups of 64 columns; teams get more
+        // blocks (fewer groups each) while they can all work: as many teams
+        // as sequences, or, of uneven lengths, as keep busy for as long as
+        // the longest sequence takes (FLASH passes over every position twice;
+        // a quarter fewer are still better off as larger teams: 64 sequences
+        // of K = 1000, T ~ U[100, 2000], take 13.2 ms on 32 teams of 8
+        // blocks, 15.6 ms on 64 of 4)
+        const int32_t groups = L.Kp / 64, budget = kTeamBlocks;
+        const int64_t roots = std::max<int64_t>(1, nonempty);
+        const int64_t work = (method == FV_FLASH ? 2 : 1) * L.sum_T;
+        const int64_t busy = std::max<int64_t>(1, std::min(roots, (work + max_T - 1) / std::max<int64_t>(1, max_T)));
+        L.team = (groups + kTeamGroups - 1) / kTeamGroups;
+        while (L.team * 2 <= groups && L.team * 2 * busy * 4 <= budget * 5) L.team *= 2;
+        L.teams = (int32_t)std::min<int64_t>(budget / L.team,
+                                             std::max(roots, method == FV_FLASH ? L.n_segs : (int64_t)0));
+        L.xch_bytes = round_up(((L.team > 1 ? 2 * (int64_t)L.Kp + 2 * round_up(groups, 16) : 0) + 16 + L.team) * 8, kAlign);
+    }
+    put(cur, L.cmax, L.teams ? (size_t)K * 4 : 0);
+    // (as many as can be resident, so that the size does not grow with P)
+    put(cur, L.xch, (size_t)(method == FV_FLASH && L.team ? kTeamBlocks / L.team : L.teams) * L.xch_bytes);
     put(cur, L.seq1, single ? sizeof(fv_seq) : 0);
     put(cur, L.seqinfo, (size_t)std::max(n_seqs, 1) * sizeof(SeqInfo));
     put(cur, L.keys, (size_t)std::max(n_seqs, 1) * 8);
@@ -361,6 +399,7 @@ void launch_transpose(const fv_trans* A, const DenseLayout& L, char* w, hipStrea
 struct DeviceInfo {
     int cus = 0;
     int engine_blocks_per_cu = 0;
+    int team_blocks_per_cu[4] = {0, 0, 0, 0};   // one block, K <= 1024, 4096, 16384
 };
 
 // Queried once per device and cached: a decode call then does no property
@@ -403,6 +442,13 @@ fv_status device_info(DeviceInfo& di) {
         HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(fv_engine_kernel),
                                                              kEngineBlock, 0));
         d.engine_blocks_per_cu = nb;
+        const void* const team[4] = {reinterpret_cast<const void*>(fv_bound1k_kernel),
+                                     reinterpret_cast<const void*>(fv_team1k_kernel),
+                                     reinterpret_cast<const void*>(fv_team4k_kernel),
+                                     reinterpret_cast<const void*>(fv_team16k_kernel)};
+        for (int k = 0; k < 4; ++k)
+            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&d.team_blocks_per_cu[k], team[k],
+                                                                 k == 0 ? kBoundBlock : kTeamBlock, 0));
         if (nb < 1) return fail(FV_E_DEVICE, "engine kernel cannot be resident");
         g_dev_info[dev] = d;
         g_dev_known[dev] = true;
@@ -420,6 +466,44 @@ bool use_wide_rows(uint32_t flags, int32_t K, int32_t n_seqs, bool sparse) {
     if (flags & FV_FLAG_WIDE_ROWS) return true;
     if (flags & FV_FLAG_LOCAL_ROWS) return false;
     return K >= 4096 || (K >= 1024 && n_seqs <= 4);
+}
+
+// Bounded decodes (fv_bound.hip) of one model: how its FLASH passes are cut
+// and how many teams run them.
+struct BoundPlan {
+    int32_t teams = 0;   // 0: the lock-step engine decodes this model
+    int32_t leaf = 0, split = 0, rows = 0;
+    int64_t scratch = 0;
+};
+
+BoundPlan plan_bounded(uint32_t flags, int32_t method, const fv_trans* A, const DenseLayout& L, const DeviceInfo& di) {
+    BoundPlan b;
+    // flags that ask for a placement, a kernel or the full bisection, and
+    // the engine's own hooks, mean the lock-step engine
+    if (!L.teams || (flags & ~(uint32_t)FV_FLAG_VALIDATE) || g_dbg_max_steps || g_dbg_spin_limit || g_dbg_trace) return b;
+    // the blocks of the teams wait for each other: all of them are resident
+    const int32_t resident = di.cus * di.team_blocks_per_cu[L.team == 1 ? 0 : (A->K <= 1024 ? 1 : (A->K <= 4096 ? 2 : 3))];
+    if (resident < L.team) return b;
+    b.teams = std::min(L.teams, resident / L.team);
+    if (method == FV_FLASH) {
+        // a team's scratch holds a leaf's backpointers or, for a longer
+        // segment, its division copies (scores and links, 8 bytes a state
+        // and division); shorter leaves where the slots hold too few long ones
+        const int64_t have = (int64_t)L.n_slots * L.slot_floats * 4;
+        b.leaf = std::max<int32_t>(16, std::min(kLeafLen, L.max_seg));
+        const int32_t want = b.teams;
+        for (;;) {
+            b.scratch = round_up((int64_t)b.leaf * L.Kp * 2, kAlign);
+            b.teams = (int32_t)std::min<int64_t>(want, have / b.scratch);
+            if (b.teams >= want || b.leaf <= 16) break;
+            b.leaf = std::max(16, b.leaf / 2);
+        }
+        b.split = b.leaf / 4;
+    }
+    // the lists hold every state up to K = 1024; beyond, a root that mostly
+    // leaves them goes to the engine, whose step costs the same whatever the scores
+    if (A->K > 1024) b.rows = 1;
+    return b;
 }
 
 // FLASH parallelism when the caller passes P <= 0.  The engine's time is
@@ -567,6 +651,20 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
     }
     std::vector<EngineArgs> args(bp.L.size());
     std::vector<const float*> aps(bp.L.size());
+    std::vector<BoundPlan> bounds(bp.L.size());
+    // vanilla or FLASH decodes whose models are all small and dense: one block per sequence, one
+    // launch per model
+    bool small = !(flags & FV_FLAG_ENGINE);
+    for (size_t p = 0; p < bp.L.size(); ++p) {
+        const int32_t K_ = bp.L[p].K;
+        small = small && models[bp.model[p]].kind == FV_DENSE &&
+                ((bp.method[p] == FV_VANILLA && K_ <= kSmallK) || (bp.method[p] == FV_FLASH && K_ <= kSmallFlashK));
+    }
+    bool engine = false;   // the lock-step engine is launched
+    for (size_t p = 0; p < bp.L.size() && !small; ++p) {
+        bounds[p] = plan_bounded(flags, bp.method[p], &models[bp.model[p]], bp.L[p], di);
+        engine = engine || bounds[p].teams == 0 || bounds[p].rows > 0;
+    }
     for (size_t p = 0; p < bp.L.size(); ++p) {
         const DenseLayout& L = bp.L[p];
         const fv_trans* A = &models[bp.model[p]];
@@ -583,21 +681,22 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         }
         const float* Ap = sparse ? nullptr : A->log_a;
         if (sparse) launch_transpose(A, L, w, stream);
-        if (!sparse && L.Kp != A->K) {
-            float* pad = static_cast<float*>(at(L.Ap));
-            const int64_t cells = (int64_t)L.Kp * L.Kp;
-            hipLaunchKernelGGL(fv_prep_dense_kernel, dim3((unsigned)((cells + kBlock - 1) / kBlock)), dim3(kBlock), 0,
-                               stream, A->log_a, A->K, L.Kp, pad);
-            Ap = pad;
-        }
-        aps[p] = Ap;
+        // copies of log A: padded, and for the engine transposed (wide rows never
+        // use that; after a bounded decode only if it left anything)
         const bool wide = use_wide_rows(flags, A->K, n_local, sparse);
-        float* At = nullptr;
-        if (L.At.bytes && !wide) {   // wide rows never use it
-            At = static_cast<float*>(at(L.At));
-            hipLaunchKernelGGL(fv_transpose_dense_kernel, dim3(L.Kp / 64, L.Kp / 64), dim3(kBlock), 0, stream, Ap,
-                               L.Kp, At);
+        const bool pad = !sparse && L.Kp != A->K;
+        if (pad) Ap = static_cast<const float*>(at(L.Ap));
+        aps[p] = Ap;
+        float* const At = L.At.bytes && !wide ? static_cast<float*>(at(L.At)) : nullptr;
+        if (pad) {
+            const int64_t cells = (int64_t)L.Kp * L.Kp;
+            hipLaunchKernelGGL(fv_prep_dense_kernel, dim3((unsigned)((cells + kBlock - 1) / kBlock)), dim3(kBlock),
+                               0, stream, A->log_a, A->K, L.Kp, const_cast<float*>(Ap));
         }
+        const BoundPlan& bnd = bounds[p];
+        if (At && !bnd.teams)
+            hipLaunchKernelGGL(fv_transpose_dense_kernel, dim3(L.Kp / 64, L.Kp / 64), dim3(kBlock), 0, stream, Ap,
+                               L.Kp, At, (const int32_t*)nullptr);
         if (validate) {
             const int64_t kk = (int64_t)A->K;
             if (sparse) {
@@ -691,6 +790,17 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         a.spin_limit = g_dbg_spin_limit ? g_dbg_spin_limit : (int64_t)1 << 24;
         // beam: exact re-decodes add at most one pass per subtask
         a.max_steps = g_dbg_max_steps ? g_dbg_max_steps : (meth == FV_BEAM ? 16 : 8) * (L.sum_T + L.n_tasks) + 4096;
+        if (bnd.teams) {
+            a.bounded = 1;
+            a.b_leaf = bnd.leaf;
+            a.b_split = bnd.split;
+            a.b_team = L.team;
+            a.cmax = static_cast<uint32_t*>(at(L.cmax));
+            a.bscr = reinterpret_cast<char*>(a.slot_base);
+            a.bscr_bytes = bnd.scratch;
+            a.bxch = static_cast<char*>(at(L.xch));
+            a.bxch_bytes = L.xch_bytes;
+        }
         if (validate) {
             a.bad_seq = bad_seq;
             a.bad_model = bad_model + p;
@@ -714,6 +824,13 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         sa.emit_kind = emit.kind;
         sa.args_out = table + p;
         hipLaunchKernelGGL(fv_setup_kernel, dim3(1), dim3(kBlock), 0, stream, a, sa);
+        if (bnd.teams) {
+            // enough row shares for about two blocks per CU
+            const int32_t chunks = (A->K + 63) / 64;
+            hipLaunchKernelGGL(fv_colmax_kernel, dim3(chunks, std::max(1, std::min(A->K / 32, 512 / chunks))),
+                               dim3(kBlock), 0, stream, A->log_a, A->K, a.cmax, reinterpret_cast<uint4*>(a.bxch),
+                               (int64_t)bnd.teams * L.xch_bytes / 16);
+        }
     }
     if (status && !single && n_models > 1)
         hipLaunchKernelGGL(fv_model_check_kernel, dim3((n_seqs + kBlock - 1) / kBlock), dim3(kBlock), 0, stream,
@@ -723,14 +840,6 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
     int32_t n_tab = (int32_t)bp.L.size();
     void* kargs[] = {&table_dev, &n_tab};
     if (g_prof_on) HIP_TRY(hipEventRecord(g_prof_ev[0], stream));
-    // vanilla or FLASH decodes whose models are all small and dense: one wave per sequence, one
-    // launch per model, no persistent engine
-    bool small = !(flags & FV_FLAG_ENGINE);
-    for (size_t p = 0; p < bp.L.size(); ++p) {
-        const int32_t Kp_ = bp.L[p].K;
-        small = small && models[bp.model[p]].kind == FV_DENSE &&
-                ((bp.method[p] == FV_VANILLA && Kp_ <= kSmallK) || (bp.method[p] == FV_FLASH && Kp_ <= kSmallFlashK));
-    }
     if (small) {
         for (size_t p = 0; p < bp.L.size(); ++p) {
             const int32_t Ks = bp.L[p].K;
@@ -750,7 +859,23 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
                                    grid, block, 0, stream, table_dev + p);
         }
     }
-    else
+    for (size_t p = 0; p < bp.L.size(); ++p) {
+        if (!bounds[p].teams) continue;
+        const int32_t K = bp.L[p].K;
+        const EngineArgs* ta = table_dev + p;
+        void* targs[] = {&ta};
+        const dim3 grid(bounds[p].teams * bp.L[p].team);
+        const void* const fn = bp.L[p].team == 1 ? reinterpret_cast<const void*>(fv_bound1k_kernel)
+                               : K <= 1024       ? reinterpret_cast<const void*>(fv_team1k_kernel)
+                               : K <= 4096       ? reinterpret_cast<const void*>(fv_team4k_kernel)
+                                                 : reinterpret_cast<const void*>(fv_team16k_kernel);
+        if (bp.L[p].team > 1) HIP_TRY(hipLaunchCooperativeKernel(fn, grid, dim3(kTeamBlock), targs, 0, stream));
+        else HIP_TRY(hipLaunchKernel(fn, grid, dim3(kBoundBlock), targs, 0, stream));
+        if (bounds[p].rows > 0 && args[p].At)
+            hipLaunchKernelGGL(fv_transpose_dense_kernel, dim3(args[p].Kp / 64, args[p].Kp / 64), dim3(kBlock), 0,
+                               stream, args[p].Acol, args[p].Kp, const_cast<float*>(args[p].At), &args[p].st->q_tail0);
+    }
+    if (engine)
         HIP_TRY(hipLaunchCooperativeKernel(reinterpret_cast<const void*>(fv_engine_kernel), dim3(n_compute + 1),
                                            dim3(kEngineBlock), kargs, 0, stream));
     if (g_prof_on) {

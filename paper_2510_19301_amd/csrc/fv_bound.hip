@@ -1,0 +1,980 @@
+// Exact decoding with bounded predecessor scans (gfx950).
+//
+// A step needs, for every destination j, the first maximum over i of
+// fl(delta_i + log A(i, j)).  With cm_j = max_i log A(i, j), a predecessor
+// whose fl(delta_i + cm_j) is below the best candidate found so far cannot
+// attain the maximum (float addition is monotone), so scanning predecessors
+// from the largest delta downwards may stop as soon as an upper bound u of
+// the deltas not yet scanned gives fl(u + cm_j) < best_j.  The stop is exact:
+// scores, backpointers and ties are those of the full scan.  Where scores
+// spread over more than a few units (any informative emission) a small part
+// of the K predecessors is read: about 160 of 1024 rows of log A per 64
+// columns with Dirichlet(0.1) transitions and N(0, 2^2) emissions, 8 of 256
+// for a CRF's.
+//
+// The decreasing order comes in kTiers lists of states, by how far their
+// scores lie below the maximum; the distances follow what the last steps
+// needed.  States below the last list are scanned only when the bound still
+// calls for them.
+//
+// Work division.  A team of M blocks decodes one task (a vanilla pass, a FLASH
+// root, a FLASH segment); each block owns up to kTeamGroups groups of 64
+// columns.  After a step each group's wave publishes its scores as 64-bit
+// words {score, tracked division state, step tag} with device-scope stores;
+// every block polls the words of the whole row, so data and synchronisation
+// are the same transfer (about 1000 clocks between any two CUs, on one XCD
+// or two; a barrier and a read would be two such trips).  There is no
+// grid-wide step: teams take tasks from a queue (longest roots first) and a
+// finished FLASH pass appends its segments.  The blocks of a team follow each
+// other in the grid, hence sit on different XCDs, so an XCD reads only its
+// blocks' columns of log A and its L2 holds them.
+//
+// Measured against the lock-step engine (a global step of 15 to 28 us for all
+// rows): K = 512 Erdos-Renyi graph, T = 512, FLASH P = 16: 7.1 -> 2.0 ms; 64
+// sequences, K = 1000, T ~ U[100, 2000], vanilla: 34.6 -> 13.3 ms; 256
+// sequences, K = 1024, T ~ U[500, 8000], FLASH P = 64: 244 -> 112 ms;
+// K = 16384, T = 512, vanilla: 102 -> 24.5 ms; K = 5001, T = 777, FLASH
+// P = 16: 39.3 -> 16.7 ms.
+#include <float.h>
+
+#include "fv_device.h"
+
+namespace fv {
+
+constexpr int kTiers = 3;
+constexpr int32_t kBoundRetry = 77;   // sequence status: left to the lock-step engine
+constexpr int kTCols = 64 * kTeamGroups;   // columns of a block, at most
+constexpr int kUnit = 8;              // list entries of a unit of work
+constexpr int kUnitLoads = kUnit / 4; // 16 lanes across 64 columns: 4 entries side by side
+
+// A candidate and its predecessor as one float64 pattern: the float32 score
+// in the high word, the state in the low word.  Finite scores and infinities
+// are finite float64 patterns, ordered first by the score, so one v_max_f64
+// per candidate keeps the maximum and where it came from, in any scan order.
+// Equal scores are decided by the low word: the smaller one is the larger
+// number for negative scores, the larger one for positive scores, so the
+// state is stored as itself while scores are negative and complemented while
+// they are positive (team_finish handles columns of the other sign, and zeros).
+struct BoundEnt {
+    int32_t lo;
+    float v;
+};
+
+// KC: the largest K, LC: states a list holds, NB: steps whose emission rows
+// are fetched, and backpointer rows stored, at once.  (Memory operations of a
+// wave complete in order, so an emission load in flight holds back every
+// log A row read after it for as long as HBM takes; in groups of NB rows that
+// wait comes once every NB steps.)
+template <int KC, int LC, int NB, bool TEAM>
+struct TeamLds {
+    union {
+        struct {
+            BoundEnt list[kTiers][LC];      // scanned states, unordered
+            float eb[2][NB * kTCols];       // emission rows of the block's columns: in use, and coming
+        };
+        uint32_t walk[(8 * kTiers * LC + 8 * NB * kTCols) / 4];   // backpointer rows being walked
+    };
+    unsigned long long part[kTCols];   // order keys of partial maxima
+    float cm[kTCols];                  // column maxima; NaN where no scan is ever needed
+    uint16_t pb[2][NB * kTCols];       // backpointer rows: being made, being stored
+    uint16_t anc[TEAM ? 1 : 2][KC];    // tracked division state of every state
+    float x[TEAM ? 1 : 2][TEAM ? 1 : KC];   // a single block's scores, by step parity
+    uint32_t rmax[2];                  // and the order key of the largest
+    int32_t cnt[2][4];                 // by step parity: states on the lists, any finite one on none
+    uint32_t need[2];                  // by step parity: the distance the groups needed (bits of a float >= 0)
+    unsigned long long key;
+    int32_t sv[8];
+};
+
+// ---------------------------------------------------------------- wave operations
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t v) {   // zero where no lane is the source
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {   // in every lane
+    v = max(v, dpp_u<0x111, 0xf>(v));   // row_shr:1
+    v = max(v, dpp_u<0x112, 0xf>(v));
+    v = max(v, dpp_u<0x114, 0xf>(v));
+    v = max(v, dpp_u<0x118, 0xf>(v));
+    v = max(v, dpp_u<0x142, 0xa>(v));   // row_bcast:15
+    v = max(v, dpp_u<0x143, 0xc>(v));   // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int32_t)v, 63);
+}
+// fmax would first quiet its operands, a second instruction for each
+__device__ __forceinline__ double max64(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double swap_max32(double a, double b) {   // low lanes: max of a's halves, high lanes: of b's
+    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return max64(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+}
+__device__ __forceinline__ double swap_max16(double a, double b) {   // even rows: max of a's row pair, odd rows: of b's
+    const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return max64(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+}
+// Merges the partial maxima of the lanes that scanned the same four columns
+// (lanes equal modulo 16) and spreads the columns over them: row r of 16 lanes
+// ends with column 4 (lane mod 16) + r.
+__device__ __forceinline__ double merge_group(const double (&b)[4]) {
+    return swap_max16(swap_max32(b[0], b[2]), swap_max32(b[1], b[3]));
+}
+__device__ __forceinline__ uint32_t score_key(float v) {
+    const uint32_t b = __float_as_uint(v);
+    return b ^ ((uint32_t)((int32_t)b >> 31) | 0x80000000u);
+}
+__device__ __forceinline__ float score_of_key(uint32_t k) {
+    return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
+}
+// a candidate pattern as an unsigned number of the same order, and back
+__device__ __forceinline__ unsigned long long pattern_key(double b) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(b);
+    return u ^ ((unsigned long long)((long long)u >> 63) | 0x8000000000000000ull);
+}
+__device__ __forceinline__ double pattern_of_key(unsigned long long k) {
+    return __longlong_as_double((long long)(k ^ ((unsigned long long)((long long)~k >> 63) | 0x8000000000000000ull)));
+}
+__device__ __forceinline__ void take1(float& best, int32_t& arg, float c, int32_t i) {
+    const bool up = c > best || (c == best && i < arg);
+    best = up ? c : best;
+    arg = up ? i : arg;
+}
+
+// Exchange buffer of a team (device-scope accesses only): the words of the
+// row by step parity, the groups' maxima by step parity, the task descriptor
+// and each block's completed-task counter.
+struct TeamBuf {
+    unsigned long long* x[2];
+    unsigned long long* g[2];
+    unsigned long long* desc;
+    unsigned long long* done;
+    unsigned long long* beyond;   // scans of the task that left the lists
+};
+__device__ __forceinline__ TeamBuf team_buf(char* base, int32_t Kp, int32_t M) {
+    unsigned long long* w = reinterpret_cast<unsigned long long*>(base);
+    if (M == 1) Kp = 0;   // a single block exchanges no scores
+    const int32_t ng = (Kp / 64 + 15) & -16;
+    TeamBuf b;
+    b.x[0] = w;
+    b.x[1] = w + Kp;
+    b.g[0] = w + 2 * (int64_t)Kp;
+    b.g[1] = b.g[0] + ng;
+    b.desc = b.g[1] + ng;
+    b.done = b.desc + 16;
+    b.beyond = b.desc + 8;
+    return b;
+}
+// score | tracked division state | stop mark | step tag (15 bits)
+constexpr uint32_t kTagBits = 0x7fff;
+__device__ __forceinline__ unsigned long long team_word(float v, uint32_t mid, uint32_t stop, uint32_t tag) {
+    return (unsigned long long)__float_as_uint(v) | ((unsigned long long)(mid | stop << 16 | tag << 17) << 32);
+}
+
+enum : int32_t { BM_VANILLA = 0, BM_DIV = 1, BM_LEAF = 2 };
+
+// W: waves of a block.
+template <int KC, int LC, int NB, bool TEAM, int W>
+__device__ __forceinline__ void team_decode(cargs_t& a) {
+    constexpr int kTThreads = 64 * W;
+    constexpr int GPW = TEAM ? kTeamGroups / W : (KC / 64 + W - 1) / W;   // groups of a wave, at most
+    // long rows: the groups' maxima are polled first, the words then read once
+    constexpr bool GATE = TEAM && KC > 4096;
+    __shared__ __align__(16) TeamLds<KC, LC, NB, TEAM> s;
+    const int32_t tid = threadIdx.x, lane = tid & 63, wv = uni(tid >> 6);
+    const int32_t K = a.K, Kp = a.Kp, M = a.b_team;
+    if (Kp > KC) return;
+    const int32_t team = blockIdx.x / M, member = blockIdx.x - team * M;
+    const int32_t ngt = Kp / 64;                                  // groups of the row,
+    const int32_t gb = ngt * member / M;                          // this block's first one
+    const int32_t ngl = ngt * (member + 1) / M - gb;              // and their number
+    const int32_t cb = gb * 64, cn = min(K, cb + ngl * 64) - cb;  // its columns
+    const TeamBuf tb = team_buf(a.bxch + (int64_t)team * a.bxch_bytes, Kp, M);
+    typedef __attribute__((address_space(1))) const char gchar_t;
+    typedef float vec_t __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(1))) const vec_t gvec_t;
+    gchar_t* const A = reinterpret_cast<gchar_t*>(reinterpret_cast<uint64_t>(a.Acol));
+    const int32_t pitch = Kp * 4;
+    EngineState* const st = a.st;
+    const int32_t n_roots = st->q_tail0;
+    // waves of a group: all of them for a single group, ..., one where there
+    // are more groups than half the waves
+    int32_t wpg = W;
+    while (wpg > 1 && wpg * ngl > W) wpg >>= 1;
+    const int32_t g0 = wv / wpg, sub = wv - g0 * wpg;             // this wave's (first) group and share of it
+    const int32_t lc4 = 4 * (lane & 15);
+    int32_t g = g0;                                               // the group being worked on, and
+    int32_t jl = g * 64 + lc4 + (lane >> 4);                      // the column (in the block) a lane ends with
+    bool active = g < ngl;
+    auto at_group = [&](int32_t k) {                              // this wave's k-th group
+        g = g0 + k * W;
+        jl = g * 64 + lc4 + (lane >> 4);
+        active = g < ngl;
+    };
+    for (int32_t k = tid; k < kTCols; k += kTThreads) {
+        const float c = k < cn ? score_of_key(a.cmax[cb + k]) : -INFINITY;
+        s.cm[k] = c > -INFINITY ? c : __builtin_nanf("");
+    }
+    const double none = __hiloint2double((int32_t)0xff800000u, 0);
+    float G = 8.0f, G1 = 16.0f;   // distance below the maximum that the scans are expected to need
+    uint32_t epoch = 1;        // tag of the scores of a task's first position
+    unsigned long long task_no = 0;
+    for (;;) {
+        // ---- next task: the team's first block takes it and tells the others
+        ++task_no;
+        if (tid == 0) {
+            unsigned long long w0 = 0, w1 = 0, w2 = 0;
+            int32_t got = 0;
+            if (member == 0) {
+                const uint32_t h =
+                    __hip_atomic_fetch_add(&st->bq_head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                got = h < (uint32_t)n_roots ? 1 : 0;
+                // spawned tasks: wait for the publication of this ticket, or for
+                // the end of every task that could still spawn (each is running
+                // on some team, so the wait ends)
+                if (!got && a.method == FV_FLASH) {
+                    for (int64_t spin = 0; spin < kTeamSpin; ++spin) {
+                        const uint32_t live = ld_c(&st->bq_live);
+                        if (ld_c(&st->bq_pub) > h) { got = 1; break; }
+                        if (live == 0) {
+                            got = ld_c(&st->bq_pub) > h ? 1 : 0;
+                            break;
+                        }
+                        __builtin_amdgcn_s_sleep(16);
+                    }
+                }
+                if (got) {
+                    const unsigned long long* p = reinterpret_cast<const unsigned long long*>(a.queue + h);
+                    w0 = ld_c(p);
+                    w1 = ld_c(p + 1);
+                    const int32_t tm = (int32_t)w1, tn = (int32_t)(w1 >> 32);
+                    if ((int32_t)(w0 >> 32) == KIND_SUB) {
+                        const SeqInfo& sq = a.seqs[(int32_t)w0];
+                        const int32_t qn = clampi(ld_c(sq.path + tn), K);
+                        const int32_t qp = tm > 0 ? clampi(ld_c(sq.path + tm - 1), K) : 0;
+                        const float al = tm > 0 ? ld_cf(a.alpha_at + sq.alpha_off + tm - 1) : 0.0f;
+                        w2 = (unsigned long long)__float_as_uint(al) | ((unsigned long long)(qn | qp << 16) << 32);
+                    }
+                }
+                st_c(tb.beyond, 0ull);
+                if (M > 1) {
+                    st_c(tb.desc + 1, w0);
+                    st_c(tb.desc + 2, w1);
+                    st_c(tb.desc + 3, w2);
+                    st_c(tb.desc + 4, (unsigned long long)got);
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                    __builtin_amdgcn_s_waitcnt(0);
+                    st_c(tb.desc, task_no);
+                }
+            } else {
+                for (int64_t spin = 0; spin < kTeamSpin; ++spin) {
+                    if (ld_c(tb.desc) == task_no) { got = 1; break; }
+                    __builtin_amdgcn_s_sleep(1);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                if (got) {
+                    w0 = ld_c(tb.desc + 1);
+                    w1 = ld_c(tb.desc + 2);
+                    w2 = ld_c(tb.desc + 3);
+                    got = (int32_t)ld_c(tb.desc + 4);
+                }
+            }
+            s.sv[0] = got;
+            s.sv[1] = (int32_t)w0;
+            s.sv[2] = (int32_t)(w0 >> 32);
+            s.sv[3] = (int32_t)w1;
+            s.sv[4] = (int32_t)(w1 >> 32);
+            s.sv[5] = (int32_t)w2;
+            s.sv[6] = (int32_t)(w2 >> 32);
+        }
+        __syncthreads();
+        if (!s.sv[0]) break;
+        const int32_t seq = uni(s.sv[1]), kind = uni(s.sv[2]), m = uni(s.sv[3]), n = uni(s.sv[4]);
+        const float alpha = __int_as_float(uni(s.sv[5]));
+        const int32_t q_n = uni(s.sv[6]) & 0xffff, q_prev = (uint32_t)uni(s.sv[6]) >> 16;
+        SeqInfo& sq = a.seqs[seq];
+        const int32_t len = n - m + 1;
+        int32_t mode = BM_VANILLA, w = 1;
+        if (kind == KIND_ROOT) {
+            mode = BM_DIV;
+            w = sq.pp;
+        } else if (kind == KIND_SUB) {
+            mode = len <= a.b_leaf ? BM_LEAF : BM_DIV;
+            w = mode == BM_DIV ? min(a.b_split, max(2, (len + a.b_leaf - 1) / a.b_leaf)) : 1;
+        }
+        // Rarely used addresses are formed where they are used (from a copy of
+        // the sequence index the compiler cannot see through), not kept in
+        // scalar registers across the steps.
+        auto seq_info = [&]() -> SeqInfo& {
+            int32_t q = seq;
+            asm volatile("" : "+s"(q));
+            return a.seqs[q];
+        };
+        auto scratch = [&]() {
+            int32_t b = team;
+            asm volatile("" : "+s"(b));
+            return a.bscr + (int64_t)b * a.bscr_bytes;
+        };
+        // division copies: scores and links of w - 1 divisions, pitch Kp
+        auto dsnap = [&]() {
+            return kind == KIND_ROOT ? a.root_copy + seq_info().root_off * (int64_t)Kp
+                                     : reinterpret_cast<float*>(scratch());
+        };
+        auto link = [&]() { return reinterpret_cast<int32_t*>(dsnap() + (int64_t)(w - 1) * Kp); };
+        // backpointer rows: the sequence's table (row t), or the leaf's (row t - m - 1)
+        const int32_t tab0 = mode == BM_VANILLA ? 0 : m + 1;
+        auto table = [&]() {
+            return mode == BM_VANILLA ? a.psi16 + seq_info().psi_off : reinterpret_cast<uint16_t*>(scratch());
+        };
+        auto div_end = [&](int32_t k) { return m + (int32_t)((((int64_t)k + 1) * len - 1) / w); };
+        // emission rows t0 .. t0 + NB - 1 into LDS (no registers held); 64 columns a wave and instruction
+        auto fetch = [&](int32_t half, int32_t t0) {
+            typedef __attribute__((address_space(3))) void lvoid_t;
+            typedef __attribute__((address_space(1))) const void gvoid_t;
+            const SeqInfo& si = seq_info();
+            const float* const lb = si.log_b + cb;
+            const int64_t ld = si.ld;
+            for (int32_t q = wv; q < ngl * NB; q += W) {
+                const int32_t r = q % NB, c = q / NB;
+                lvoid_t* dst = reinterpret_cast<lvoid_t*>((uint32_t)__builtin_amdgcn_readfirstlane(
+                    (int32_t)(uintptr_t)&s.eb[half][r * kTCols + c * 64]));
+                if (t0 + r <= n && c * 64 + lane < cn)
+                    __builtin_amdgcn_global_load_lds(
+                        reinterpret_cast<gvoid_t*>(
+                            reinterpret_cast<uintptr_t>(lb + (int64_t)(t0 + r) * ld + c * 64 + lane)),
+                        dst, 4, 0, 0);
+            }
+        };
+        // the block's part of cnt finished backpointer rows t0 ..
+        auto flush = [&](int32_t half, int32_t t0, int32_t cnt) {
+            const uint16_t* const rows = s.pb[half];
+            uint16_t* const dst = table() + (int64_t)(t0 - tab0) * K + cb;
+            if (K & 1) {
+                for (int32_t k = tid; k < cnt * kTCols; k += kTThreads) {
+                    const int32_t c = k % kTCols;
+                    if (c < cn) st_c(dst + (int64_t)(k / kTCols) * K + c, rows[k]);
+                }
+            } else {
+                for (int32_t k = tid; k < cnt * (kTCols / 2); k += kTThreads) {
+                    const int32_t c = 2 * (k % (kTCols / 2));
+                    if (c < cn)
+                        st_c(reinterpret_cast<uint32_t*>(dst + (int64_t)(k / (kTCols / 2)) * K + c),
+                             reinterpret_cast<const uint32_t*>(rows)[k]);
+                }
+            }
+        };
+        if (n > m) fetch(0, m + 1);
+
+        // ---- start vector: published under the task's first tag
+        int32_t d_next = 0;
+        int32_t e_next = mode == BM_DIV && w > 1 ? div_end(0) : -1, e_prev = -1;
+        const int32_t e_first = e_next;
+        uint32_t give_up = 0;      // the first group's mark: this task is left to the engine
+        auto publish = [&](int32_t t, float xn, int32_t mid) {
+            const uint32_t tag = (epoch + (uint32_t)(t - m)) & kTagBits;
+            const int32_t p = (int32_t)(epoch + (uint32_t)(t - m)) & 1;
+            if constexpr (TEAM) {
+                if (jl < cn) st_c(tb.x[p] + cb + jl, team_word(xn, (uint32_t)mid, give_up, tag));
+            } else {
+                s.x[p][jl] = xn;
+                if (mode == BM_DIV) s.anc[p][jl] = (uint16_t)mid;
+            }
+            if constexpr (!TEAM || GATE) {
+                const uint32_t mk = wave_max(score_key(xn));
+                if (lane == 0) {
+                    if constexpr (TEAM) st_c(tb.g[p] + gb + g, (unsigned long long)mk | ((unsigned long long)tag << 48));
+                    else atomicMax(&s.rmax[p], mk);
+                }
+            }
+        };
+        if (tid < 2) {
+            s.rmax[tid] = s.need[tid] = 0;
+            s.cnt[tid][0] = s.cnt[tid][1] = s.cnt[tid][2] = s.cnt[tid][3] = 0;
+        }
+        __syncthreads();
+        for (int k = 0; k < GPW; ++k) {
+            if (GPW > 1) at_group(k);
+            if (!active || sub != 0) break;
+            float x = -INFINITY;
+            if (jl < cn) {
+                const int32_t j = cb + jl;
+                const float b = as_global(sq.log_b)[(int64_t)m * sq.ld + j];
+                if (m > 0) x = (alpha + a.Acol[(int64_t)q_prev * Kp + j]) + b;
+                else x = a.log_pi ? a.log_pi[j] + b : b;
+                if (e_next == m) st_cf(dsnap() + j, x);
+            }
+            publish(m, x, 0);
+        }
+        if (e_next == m) {
+            e_prev = m;
+            d_next = 1;
+            e_next = w > 2 ? div_end(1) : -1;
+        }
+        bool retry = false;
+        for (int32_t t = m + 1; t <= n; ++t) {
+            const int32_t step = t - m - 1, row = step % NB, half = (step / NB) & 1, par = step & 1;
+            const uint32_t tag = (epoch + (uint32_t)step) & kTagBits;
+            const int32_t xp = (int32_t)(epoch + (uint32_t)step) & 1;
+            if (row == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's rows of the half in use
+            // ---- the previous scores and the largest of them
+            constexpr int NS = KC / kTThreads;   // states of a thread
+            constexpr int CN = NS < 4 ? NS : 4;
+            unsigned long long v[CN];
+            auto poll = [&](int32_t c) {   // words of states tid + c kTThreads, ...
+                for (int64_t spin = 0; spin < kTeamSpin; ++spin) {
+                    bool bad = false;
+#pragma unroll
+                    for (int k = 0; k < CN; ++k) {
+                        const int32_t i = tid + (c + k) * kTThreads;
+                        v[k] = (unsigned long long)(tag << 17) << 32 | 0xff800000u;
+                        if (i < K) v[k] = ld_c(tb.x[xp] + i);
+                    }
+#pragma unroll
+                    for (int k = 0; k < CN; ++k) bad = bad || (uint32_t)(v[k] >> 49) != tag;
+                    if (__builtin_amdgcn_ballot_w64(bad) == 0) break;
+                    if (spin == kTeamSpin - 1) st_c(&st->error, 1);
+                }
+                if (c == 0 && tid == 0) s.sv[7] = (int32_t)(v[0] >> 48) & 1;
+            };
+            if constexpr (TEAM && !GATE) {
+                poll(0);
+                uint32_t mk = 0;
+#pragma unroll
+                for (int k = 0; k < CN; ++k) mk = max(mk, score_key(__uint_as_float((uint32_t)v[k])));
+                mk = wave_max(mk);
+                if (lane == 0) atomicMax(&s.rmax[xp], mk);
+            }
+            if constexpr (GATE) {
+                if (wv == 0) {   // one wave polls the groups' maxima: more would slow what they wait for
+                    uint32_t mk = 0;
+                    for (int32_t k0 = 0; k0 < ngt; k0 += 64) {
+                        const bool in = k0 + lane < ngt;
+                        unsigned long long q = 0;
+                        for (int64_t spin = 0; spin < kTeamSpin; ++spin) {
+                            if (in) q = ld_c(tb.g[xp] + k0 + lane);
+                            if (__builtin_amdgcn_ballot_w64(in && (uint32_t)(q >> 48) != tag) == 0) break;
+                            if (spin == kTeamSpin - 1) st_c(&st->error, 1);
+                        }
+                        if (in) mk = max(mk, (uint32_t)q);
+                    }
+                    mk = wave_max(mk);
+                    if (lane == 0) s.rmax[xp] = mk;
+                }
+            }
+            __syncthreads();
+            const float D = score_of_key((uint32_t)uni((int32_t)s.rmax[xp]));
+            // a task's first step, from one state's scores, needs more than the others
+            if (step > 0) {
+                const float u = __uint_as_float((uint32_t)uni((int32_t)s.need[par]));
+                if (step == 1) G1 = fmaxf(G1 + 0.5f * (u - G1), 1e-4f);
+                else G = fmaxf(G + 0.25f * (u - G), 1e-4f);
+            }
+            const bool neg = D < 0.0f;
+            const int32_t flip = neg ? 0 : -1;
+            // ---- the lists
+            // scores from which a state is on the first, second, third list: the
+            // first holds what all groups are expected to need, or, where each
+            // wave has its own group and looks at the bound, what most of them need
+            float h0, h1, h2;
+            for (int32_t go = 0;; ++go) {
+            const float gx = (step == 0 ? G1 : G) * __int_as_float((127 - go) << 23);
+            h0 = D - (wpg > 1 ? 1.0f : 0.75f) * gx;
+            h1 = D - (wpg > 1 ? 1.2f : 1.0f) * gx;
+            h2 = D - (GATE ? 1.4f : (wpg > 1 ? 1.7f : 1.35f)) * gx;
+#pragma unroll
+            for (int c = 0; c < NS; c += CN) {
+                if (c * kTThreads >= K) break;
+                float x[CN];
+                if constexpr (TEAM) {
+                    if constexpr (GATE) poll(c);
+#pragma unroll
+                    for (int k = 0; k < CN; ++k) {
+                        const int32_t i = tid + (c + k) * kTThreads;
+                        x[k] = i < K ? __uint_as_float((uint32_t)v[k]) : -INFINITY;
+                        if (i < K && mode == BM_DIV) s.anc[0][i] = (uint16_t)(v[k] >> 32);
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < CN; ++k) {
+                        const int32_t i = tid + (c + k) * kTThreads;
+                        x[k] = i < K ? s.x[xp][i] : -INFINITY;
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < CN; ++k) {
+                    const bool fin = x[k] > -INFINITY;
+                    const uint64_t c0 = __builtin_amdgcn_ballot_w64(fin && x[k] >= h0);
+                    const uint64_t c1 = __builtin_amdgcn_ballot_w64(fin && x[k] >= h1);
+                    const uint64_t c2 = __builtin_amdgcn_ballot_w64(fin && x[k] >= h2);
+                    if (__builtin_amdgcn_ballot_w64(fin) & ~c2)
+                        if (lane == 0) s.cnt[par][3] = 1;
+                    if (c2 == 0) continue;
+                    const int32_t n0 = __popcll(c0), n1 = __popcll(c1) - n0, n2 = __popcll(c2) - n0 - n1;
+                    const int32_t add = lane == 0 ? n0 : (lane == 1 ? n1 : n2);
+                    int32_t at = 0;
+                    if (lane < kTiers) at = atomicAdd(&s.cnt[par][lane], add);
+                    const int32_t a0 = __builtin_amdgcn_readlane(at, 0), a1 = __builtin_amdgcn_readlane(at, 1),
+                                  a2 = __builtin_amdgcn_readlane(at, 2);
+                    const int32_t l = x[k] >= h0 ? 0 : (x[k] >= h1 ? 1 : 2);
+                    const uint64_t my = l == 0 ? c0 : (l == 1 ? c1 & ~c0 : c2 & ~c1);
+                    const int32_t pos = (l == 0 ? a0 : (l == 1 ? a1 : a2)) +
+                                        __builtin_amdgcn_mbcnt_hi((uint32_t)(my >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)my, 0));
+                    if (fin && x[k] >= h2 && (LC >= KC || pos < LC))
+                        s.list[l][pos] = BoundEnt{(tid + (c + k) * kTThreads) ^ flip, x[k]};
+                }
+            }
+            if (LC >= KC || go == 8) break;
+            // a first list beyond its room: a shorter reach
+            __syncthreads();
+            const bool fits = s.cnt[par][0] <= LC;
+            __syncthreads();
+            if (fits) break;
+            if (tid < 4) s.cnt[par][tid] = 0;
+            __syncthreads();
+            }
+            if (wpg > 1)
+                for (int32_t k = tid; k < kTCols; k += kTThreads) s.part[k] = 0;
+            if (tid == 0) s.need[par ^ 1] = 0;   // every wave is past its reads of the step before
+            if (tid == 1) s.rmax[xp ^ 1] = 0;
+            const bool quit = TEAM && LC < KC && s.sv[7] != 0;
+            __syncthreads();
+            if (quit) {   // its scans mostly leave the lists: the bound does not prune this
+                retry = true;                   // input, and the engine's step costs the same whatever the scores
+                break;
+            }
+            if (row == 0) {
+                fetch(half ^ 1, t + NB);   // the readers of that half are past the barrier
+                if (mode != BM_DIV && step > 0) flush(half ^ 1, t - NB, NB);
+            }
+            if (tid < 4) s.cnt[par ^ 1][tid] = 0;
+            // complete lists, and whether any finite score lies below them
+            int32_t lists = kTiers;
+            const int4 cn4 = *reinterpret_cast<const int4*>(s.cnt[par]);
+            if constexpr (LC < KC) lists = uni(cn4.x) > LC ? 0 : (uni(cn4.y) > LC ? 1 : (uni(cn4.z) > LC ? 2 : 3));
+            const bool outside = uni(cn4.w) != 0 || lists < kTiers;
+            // above every score outside the first n lists
+            auto below = [&](int32_t n) { return n == 0 ? INFINITY : (n == 1 ? h0 : (n == 2 ? h1 : h2)); };
+            // ---- scan of the groups' columns
+            const int32_t mul = neg ? pitch : -pitch;   // row offset of a list entry from its stored form
+            const int32_t add0 = cb * 4 - (neg ? 0 : pitch);
+            // entries of a list of cnt from `at` on (the last one repeated past its end)
+            auto load = [&](auto& en, auto& av, const BoundEnt* list, int32_t at, int32_t cnt, int32_t add) {
+                constexpr int N = sizeof(en) / sizeof(en[0]);
+#pragma unroll
+                for (int u = 0; u < N; ++u) en[u] = list[min(at + (lane >> 4) + u * 4, cnt - 1)];
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+                    av[u] = *reinterpret_cast<gvec_t*>(A + (uint32_t)(__mul24(en[u].lo, mul) + add));
+                __builtin_amdgcn_sched_barrier(0);   // every load is issued before the next wait
+            };
+            auto scan = [&](double (&best)[4], const auto& en, const auto& av) {
+                constexpr int N = sizeof(en) / sizeof(en[0]);
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        best[c] = max64(best[c], __hiloint2double(__float_as_int(en[u].v + av[u][c]), en[u].lo));
+            };
+            auto score_at = [&](int32_t i) {
+                if constexpr (TEAM) return __uint_as_float((uint32_t)ld_c(tb.x[xp] + i));
+                else return s.x[xp][i];
+            };
+            // the result of this wave's group from its first `done` lists and, out,
+            // the best (fo, qo) of the states outside them: the sign check, the
+            // score, the state and the division state
+            auto finish = [&](double top, int32_t done, bool out, float fo, int32_t qo) {
+                // scores of the other sign, or zeros, where the low word does not
+                // order equal candidates: compare by value and state
+                const float b0 = __int_as_float(__double2hiint(top));
+                const bool odd = neg ? b0 >= 0.0f : (b0 <= 0.0f && b0 > -INFINITY);
+                if (__builtin_amdgcn_ballot_w64(odd)) {
+                    float f = -INFINITY;
+                    int32_t q = 0;
+                    gfloat_t* const ak = as_global(a.Acol) + cb + jl;
+                    for (int32_t l = 0; l < done; ++l) {
+                        const int32_t cnt = uni(s.cnt[par][l]);
+                        for (int32_t p = 0; p < cnt; p += 8) {
+                            BoundEnt en[8];
+                            float v[8];
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) en[u] = s.list[l][min(p + u, cnt - 1)];
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) v[u] = ak[(uint32_t)(en[u].lo ^ flip) * (uint32_t)Kp];
+#pragma unroll
+                            for (int u = 0; u < 8; ++u) take1(f, q, en[u].v + v[u], en[u].lo ^ flip);
+                        }
+                    }
+                    if (out) take1(f, q, fo, qo);
+                    top = __hiloint2double(__float_as_int(f), q ^ flip);
+                }
+                const float b = __int_as_float(__double2hiint(top));
+                const int32_t arg = b > -INFINITY ? __double2loint(top) ^ flip : 0;
+                const float xn = jl < cn ? b + s.eb[half][row * kTCols + jl] : -INFINITY;
+                int32_t mid = 0;
+                if (mode == BM_DIV) {
+                    mid = e_prev == t - 1 ? arg : (t > e_first + 1 ? s.anc[TEAM ? 0 : xp][arg] : 0);
+                    if (t == e_next && jl < cn) {
+                        st_cf(dsnap() + (int64_t)d_next * Kp + cb + jl, xn);
+                        if (d_next >= 1) st_c(link() + (int64_t)d_next * Kp + cb + jl, mid);
+                    }
+                } else {
+                    s.pb[half][row * kTCols + jl] = (uint16_t)arg;
+                }
+                publish(t, xn, mid);
+                // what the next step's lists are made from, off the path of its scores
+                const float nd = D - (b - s.cm[jl]);   // NaN where nothing is needed
+                const uint32_t mx = wave_max(nd > 0.0f && nd < INFINITY ? __float_as_uint(nd) : 0u);
+                if (lane == 0) atomicMax(&s.need[par ^ 1], mx);
+                if (TEAM && LC < KC) {
+                    if (out && lane == 0)
+                        __hip_atomic_fetch_add(tb.beyond, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (member == 0 && g == 0 && (step & 15) == 15)
+                        give_up = ld_c(tb.beyond) > (unsigned long long)ngt * (unsigned long long)(8 + step / 8) ? 1u : 0u;
+                }
+            };
+#pragma unroll 1
+            for (int gi = 0; gi < GPW; ++gi) {
+            if (GPW > 1) {
+                at_group(gi);
+                if (!active && wpg == 1) break;
+            }
+            double best[4] = {none, none, none, none};
+            const int32_t add = (g * 64 + lc4) * 4 + add0;
+            // the waves of a group share its first lists (the first alone when
+            // the group is one wave's) without a look at the bound
+            int32_t k = 0;
+            if (active) {
+                for (; k < min(wpg > 1 ? 2 : 1, lists); ++k) {
+                    const BoundEnt* const list = s.list[k];
+                    const int32_t cnt = uni(s.cnt[par][k]), inc = wpg * kUnit;
+                    BoundEnt e0[kUnitLoads], e1[kUnitLoads];
+                    vec_t v0[kUnitLoads], v1[kUnitLoads];
+                    int32_t e = sub * kUnit;
+                    if (e >= cnt) continue;
+                    load(e0, v0, list, e, cnt, add);
+                    for (; e + 2 * inc < cnt; e += 2 * inc) {
+                        load(e1, v1, list, e + inc, cnt, add);
+                        scan(best, e0, v0);
+                        load(e0, v0, list, e + 2 * inc, cnt, add);
+                        scan(best, e1, v1);
+                    }
+                    if (e + inc < cnt) {
+                        load(e1, v1, list, e + inc, cnt, add);
+                        scan(best, e0, v0);
+                        scan(best, e1, v1);
+                    } else {
+                        scan(best, e0, v0);
+                    }
+                }
+            }
+            k = min(wpg > 1 ? 2 : 1, lists);
+            double top = merge_group(best);
+            if (wpg > 1) {
+                if (active) atomicMax(&s.part[jl], pattern_key(top));
+                __syncthreads();
+                if (active) top = pattern_of_key(s.part[jl]);
+            }
+            if (active && sub == 0) {
+                // true when nothing outside the first k lists can win a column
+                auto closed = [&]() {
+                    return __builtin_amdgcn_ballot_w64(below(k) + s.cm[jl] >= __int_as_float(__double2hiint(top))) == 0;
+                };
+                bool stop = k > 0 && closed();
+                while (!stop && k < lists) {
+                    const int32_t cnt = uni(s.cnt[par][k]);
+                    double more[4] = {none, none, none, none};
+                    for (int32_t e = 0; e < cnt; e += 2 * kUnit) {
+                        BoundEnt e0[2 * kUnitLoads];
+                        vec_t v0[2 * kUnitLoads];
+                        load(e0, v0, s.list[k], e, cnt, add);
+                        scan(more, e0, v0);
+                    }
+                    ++k;
+                    top = max64(top, merge_group(more));
+                    stop = closed();
+                }
+                // states outside the lists, where the bound still asks for them
+                const bool out = !stop && outside;
+                float fo = -INFINITY;
+                int32_t qo = 0;
+                if (out) {
+                    // none that scores below thr can win (checked, not derived: the
+                    // subtraction is rounded)
+                    const float bs = __int_as_float(__double2hiint(top)), cm = s.cm[jl];
+                    const float nd = D - (bs - cm);
+                    const float lim = __uint_as_float(wave_max(nd > 0.0f ? __float_as_uint(nd) : 0u));
+                    float thr = D - lim * 1.001f - 1e-6f * fabsf(D);
+                    if (__builtin_amdgcn_ballot_w64(cm == cm && !(thr + cm < bs))) thr = -FLT_MAX;
+                    const float top_of = below(k);
+                    gfloat_t* const ak = as_global(a.Acol) + cb + jl;
+                    for (int32_t c0 = 0; c0 < K; c0 += 256) {
+                        float xo[4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u)
+                            xo[u] = score_at(min(c0 + u * 64 + lane, K - 1));
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) {
+                            const bool in = c0 + u * 64 + lane < K && xo[u] >= thr && xo[u] < top_of;
+                            uint64_t mask = __builtin_amdgcn_ballot_w64(in);
+                            while (mask) {   // four rows in flight
+                                int32_t r[4];
+                                float v[4];
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) {
+                                    r[q] = mask ? (int32_t)__builtin_ctzll(mask) : r[q ? q - 1 : 0];
+                                    mask &= mask - 1;
+                                    v[q] = ak[(uint32_t)(c0 + u * 64 + r[q]) * (uint32_t)Kp];
+                                }
+#pragma unroll
+                                for (int q = 0; q < 4; ++q)
+                                    take1(fo, qo,
+                                          __int_as_float(__builtin_amdgcn_readlane(__float_as_int(xo[u]), r[q])) + v[q],
+                                          c0 + u * 64 + r[q]);
+                            }
+                        }
+                    }
+                    top = max64(top, __hiloint2double(__float_as_int(fo), qo ^ flip));
+                }
+                finish(top, k, out, fo, qo);
+            }
+            if (wpg > 1) break;
+            }
+            if (t == e_next) {
+                e_prev = t;
+                ++d_next;
+                e_next = d_next < w - 1 ? div_end(d_next) : -1;
+            }
+        }
+        // ---- end of the pass: every block's stores complete, then its counter
+        __syncthreads();
+        if (mode != BM_DIV && n > m && !retry) {
+            const int32_t cnt = (n - m - 1) % NB + 1;
+            flush(((n - m - 1) / NB) & 1, n - cnt + 1, cnt);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        const int32_t xe = (int32_t)(epoch + (uint32_t)(n - m)) & 1;   // the last scores' parity
+        epoch += (uint32_t)(len + 1 + (len == 1));   // both parities' words are rewritten by any two tasks
+        if (M > 1) {
+            if (member != 0) {
+                if (tid == 0) st_c(tb.done + member, task_no);
+                continue;
+            }
+            for (int32_t k = 1 + tid; k < M; k += kTThreads)
+                for (int64_t spin = 0; spin < kTeamSpin; ++spin) {
+                    if (ld_c(tb.done + k) == task_no) break;
+                    __builtin_amdgcn_s_sleep(1);
+                }
+            __syncthreads();
+        }
+        auto last_x = [&](int32_t j) {
+            if constexpr (TEAM) return __uint_as_float((uint32_t)ld_c(tb.x[xe] + j));
+            else return s.x[xe][j];
+        };
+        int32_t q_end = q_n;
+        bool feasible = true;
+        if (retry) {
+            if (tid == 0) st_c(&sq.status, kBoundRetry);
+            feasible = false;
+        } else if (kind != KIND_SUB) {
+            // the largest score and its lowest state (-0 and +0 equal)
+            if (tid == 0) s.key = 0;
+            __syncthreads();
+            unsigned long long key = 0;
+            for (int32_t j = tid; j < K; j += kTThreads) {
+                const unsigned long long o = order_key(last_x(j), j);
+                key = o > key ? o : key;
+            }
+            atomicMax(&s.key, key);
+            __syncthreads();
+            q_end = clampi((int32_t)(0xFFFFFFFFu - (uint32_t)(s.key & 0xFFFFFFFFull)), K);
+            const float score = last_x(q_end);
+            feasible = score != -INFINITY;
+            if (!feasible)
+                for (int32_t t = tid; t <= n; t += kTThreads) st_c(sq.path + t, -1);
+            if (tid == 0) {
+                st_cf(sq.score, score);
+                if (feasible) st_c(sq.path + n, q_end);
+                else st_c(&sq.status, (int32_t)FV_E_INFEASIBLE);
+            }
+        }
+        if (feasible && mode != BM_DIV) {
+            // walk the backpointer rows t = n .. m + 1 from q_end; short rows are
+            // copied to LDS in chunks, of long ones only the entries on the path
+            // are read
+            const uint16_t* const tab = table();
+            int32_t* const path = sq.path;
+            int32_t q = q_end;
+            constexpr int32_t cap = (int32_t)(sizeof(s.walk) / 4);
+            const int32_t w2 = (K + 1) / 2, per = KC <= 4096 && !(K & 1) ? min(cap / w2, 64) : 0;
+            if (per >= 4) {
+                for (int32_t hi = n; hi > m; hi -= per) {
+                    const int32_t lo = max(m + 1, hi - per + 1), cnt = (hi - lo + 1) * w2;
+                    const uint32_t* src = reinterpret_cast<const uint32_t*>(tab + (int64_t)(lo - tab0) * K);
+                    __syncthreads();
+                    for (int32_t k = tid; k < cnt; k += 8 * kTThreads) {
+                        uint32_t v[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            v[u] = k + u * kTThreads < cnt ? ld_c(src + k + u * kTThreads) : 0;
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            if (k + u * kTThreads < cnt) s.walk[k + u * kTThreads] = v[u];
+                    }
+                    __syncthreads();
+                    if (tid == 0) {
+                        for (int32_t t = hi; t >= lo; --t) {
+                            q = clampi(reinterpret_cast<const uint16_t*>(s.walk)[(t - lo) * K + q], K);
+                            st_cg(path + t - 1, q);
+                        }
+                        s.sv[7] = q;
+                    }
+                    __syncthreads();
+                    q = s.sv[7];
+                }
+            } else if (tid == 0) {
+                for (int32_t t = n; t > m; --t) {
+                    q = clampi(ld_c(tab + (int64_t)(t - tab0) * K + q), K);
+                    st_cg(path + t - 1, q);
+                }
+            }
+            if (tid == 0 && mode == BM_VANILLA) st_c(&sq.walked, 1);
+            __syncthreads();
+        } else if (feasible && w > 1) {
+            // division states and scores, last to first, then the segments between them
+            if (tid == 0) {
+                const float* const ds = dsnap();
+                const int32_t* const dl = link();
+                int32_t q;
+                if constexpr (TEAM) q = clampi((int32_t)(uint16_t)(ld_c(tb.x[xe] + q_end) >> 32), K);
+                else q = clampi(s.anc[xe][q_end], K);
+                for (int32_t d = w - 2; d >= 0; --d) {
+                    const int32_t e = div_end(d);
+                    st_cg(sq.path + e, q);
+                    const float al = ld_cf(ds + (int64_t)d * Kp + q);
+                    if (d >= 1) q = clampi(ld_c(dl + (int64_t)d * Kp + q), K);
+                    st_cf(a.alpha_at + sq.alpha_off + e, al);
+                }
+            }
+            if (wv == 0) {
+                int32_t cnt = 0;
+                for (int32_t k0 = 0; k0 < w; k0 += 64) {
+                    const int32_t k = k0 + lane;
+                    const bool seg = k < w && (k == w - 1 ? n : div_end(k)) > (k == 0 ? m : div_end(k - 1) + 1);
+                    cnt += __popcll(__builtin_amdgcn_ballot_w64(seg));
+                }
+                uint32_t pos = 0;
+                if (lane == 0 && cnt > 0) {
+                    pos = __hip_atomic_fetch_add(&st->bq_res, (uint32_t)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(&st->bq_live, (uint32_t)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+                pos = (uint32_t)uni((int32_t)pos);
+                uint32_t at = pos;
+                for (int32_t k0 = 0; k0 < w; k0 += 64) {
+                    const int32_t k = k0 + lane;
+                    const int32_t lo = k == 0 ? m : div_end(k - 1) + 1, hi = k >= w - 1 ? n : div_end(k);
+                    const bool seg = k < w && hi > lo;
+                    const uint64_t mask = __builtin_amdgcn_ballot_w64(seg);
+                    if (seg) {
+                        const uint32_t p = at + (uint32_t)__popcll(mask & ((1ull << lane) - 1));
+                        if ((int64_t)p < a.q_cap) {
+                            uint64_t* q = reinterpret_cast<uint64_t*>(a.queue + p);
+                            st_c(q, (uint64_t)(uint32_t)seq | ((uint64_t)KIND_SUB << 32));
+                            st_c(q + 1, (uint64_t)(uint32_t)lo | ((uint64_t)(uint32_t)hi << 32));
+                        }
+                    }
+                    at += (uint32_t)__popcll(mask);
+                }
+                // path, scores and tasks are at the memory side before the publication
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                __builtin_amdgcn_s_waitcnt(0);
+                if (lane == 0 && cnt > 0) {
+                    // publications follow the reservations' order (the earlier one is
+                    // being written by a running block)
+                    for (int64_t spin = 0; spin < kTeamSpin && ld_c(&st->bq_pub) != pos; ++spin)
+                        __builtin_amdgcn_s_sleep(1);
+                    __hip_atomic_fetch_add(&st->bq_pub, (uint32_t)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                }
+            }
+        }
+        __syncthreads();
+        if (tid == 0)
+            __hip_atomic_fetch_sub(&st->bq_live, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // ---- the last block leaves the sequences it could not decode to the engine
+    __syncthreads();
+    if (tid == 0) {
+        __builtin_amdgcn_s_waitcnt(0);
+        s.sv[0] = __hip_atomic_fetch_add(&st->bq_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
+    }
+    __syncthreads();
+    if (!s.sv[0] || wv != 0) return;
+    int32_t left = 0;
+    for (int32_t k0 = 0; k0 < n_roots; k0 += 64) {
+        const int32_t k = k0 + lane;
+        Task tk{};
+        bool again = false;
+        if (k < n_roots) {
+            tk = a.queue[k];
+            again = ld_c(&a.seqs[tk.seq].status) == kBoundRetry;
+        }
+        const uint64_t mask = __builtin_amdgcn_ballot_w64(again);
+        if (again) {
+            a.queue[left + __popcll(mask & ((1ull << lane) - 1))] = tk;
+            st_c(&a.seqs[tk.seq].status, (int32_t)FV_OK);
+        }
+        left += __popcll(mask);
+    }
+    if (lane == 0) st->q_tail0 = left;
+}
+
+// One block per task for K <= 1024, teams for K <= 1024, 4096 and 16384; a
+// block takes a CU's 16 wavefronts (two blocks of 8 for one task each: 158
+// instead of 112 ms for 256 sequences of K = 1024, T ~ U[500, 8000], FLASH
+// P = 64, whose roots then leave half of them idle).
+#define FV_TEAM(NAME, KC, LC, NB, TEAM, W)                                                                    \
+    extern "C" __global__ __launch_bounds__(64 * W, 4) void NAME(const EngineArgs* __restrict__ table) {       \
+        team_decode<KC, LC, NB, TEAM, W>(*reinterpret_cast<cargs_t*>(reinterpret_cast<uint64_t>(table)));     \
+    }
+FV_TEAM(fv_bound1k_kernel, 1024, 1024, 4, false, 16)
+FV_TEAM(fv_team1k_kernel, 1024, 1024, 4, true, 16)
+FV_TEAM(fv_team4k_kernel, 4096, 2048, 4, true, 16)
+FV_TEAM(fv_team16k_kernel, 16384, 2048, 2, true, 16)
+#undef FV_TEAM
+
+// Column maxima of log A as order keys (cmax zeroed before): each block takes
+// 64 columns of a share of the rows.  Also clears the teams' exchange buffers
+// (nzero 16-byte words).
+extern "C" __global__ __launch_bounds__(kBlock) void fv_colmax_kernel(const float* __restrict__ log_a, int32_t K,
+                                                                      uint32_t* __restrict__ cmax,
+                                                                      uint4* __restrict__ zero, int64_t nzero) {
+    const int64_t nthreads = (int64_t)gridDim.x * gridDim.y * kBlock;
+    for (int64_t k = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kBlock + threadIdx.x; k < nzero; k += nthreads)
+        zero[k] = uint4{0, 0, 0, 0};
+    __shared__ float part[kWaves][64];
+    const int32_t c = threadIdx.x & 63, r = threadIdx.x >> 6;
+    const int32_t j = blockIdx.x * 64 + c;
+    float v0 = -INFINITY, v1 = -INFINITY, v2 = -INFINITY, v3 = -INFINITY;
+    const int32_t step = (int32_t)gridDim.y * kWaves;
+    if (j < K) {
+        int32_t i = blockIdx.y * kWaves + r;
+        for (; i + 3 * step < K; i += 4 * step) {
+            v0 = fmaxf(v0, log_a[(int64_t)i * K + j]);
+            v1 = fmaxf(v1, log_a[(int64_t)(i + step) * K + j]);
+            v2 = fmaxf(v2, log_a[(int64_t)(i + 2 * step) * K + j]);
+            v3 = fmaxf(v3, log_a[(int64_t)(i + 3 * step) * K + j]);
+        }
+        for (; i < K; i += step) v0 = fmaxf(v0, log_a[(int64_t)i * K + j]);
+    }
+    part[r][c] = fmaxf(fmaxf(v0, v1), fmaxf(v2, v3));
+    __syncthreads();
+    if (r == 0 && j < K) {
+        const float m = fmaxf(fmaxf(part[0][c], part[1][c]), fmaxf(part[2][c], part[3][c]));
+        atomicMax(&cmax[j], score_key(m));
+    }
+}
+
+}  // namespace fv

@@ -29,139 +29,17 @@
 // (strictly greater group maximum wins, so the earliest group keeps ties) and
 // refined once per output inside the winning group, recomputing the exact
 // candidates; the stored value is that winning candidate.
-#include "fv_internal.h"
+#include "fv_device.h"
 
 namespace fv {
 
 static_assert(sizeof(Row) == 64, "Row is moved as 8 coherent 64-bit words");
-
-// The engine reads its arguments from a copy in the workspace through the
-// constant address space: field loads are scalar loads in every function.
-typedef __attribute__((address_space(4))) const EngineArgs cargs_t;
-// the argument block is the same for every lane: keep its address scalar
-__device__ __forceinline__ cargs_t& uniform_args(cargs_t& a) {
-    const uint64_t v = reinterpret_cast<uint64_t>(&a);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return *reinterpret_cast<cargs_t*>(((uint64_t)hi << 32) | lo);
-}
 
 // The engine runs one 1024-thread block per CU: 16 waves = 4 tile groups of
 // 4 waves (one wave per SIMD each), which keeps 4 waves per SIMD for latency
 // hiding while the step barrier has one participant per CU.
 constexpr int kEngBlock = 1024;
 constexpr int kEngWaves = kEngBlock / 64;
-
-// ---------------------------------------------------------------- access helpers
-template <typename T>
-__device__ __forceinline__ T ld_c(const T* p) {  // coherent across XCDs
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ __forceinline__ void st_c(T* p, T v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// st_c on a pointer known to address global memory: a global (not flat)
-// store, so waiting for LDS results does not also wait for it
-template <typename T>
-__device__ __forceinline__ void st_cg(T* p, T v) {
-    typedef __attribute__((address_space(1))) T gT;
-    __hip_atomic_store(reinterpret_cast<gT*>(reinterpret_cast<uint64_t>(p)), v, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float ld_cf(const float* p) {
-    return __uint_as_float(ld_c(reinterpret_cast<const uint32_t*>(p)));
-}
-__device__ __forceinline__ void st_cf(float* p, float v) {
-    st_c(reinterpret_cast<uint32_t*>(p), __float_as_uint(v));
-}
-__device__ __forceinline__ Row ld_row(const Row* p) {
-    const uint64_t* q = reinterpret_cast<const uint64_t*>(p);
-    uint64_t w[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) w[k] = ld_c(q + k);
-    Row r;
-    __builtin_memcpy(&r, w, sizeof r);
-    return r;
-}
-__device__ __forceinline__ void st_row(Row* p, const Row& r) {
-    uint64_t w[8];
-    __builtin_memcpy(w, &r, sizeof r);
-    uint64_t* q = reinterpret_cast<uint64_t*>(p);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) st_c(q + k, w[k]);
-}
-__device__ __forceinline__ int32_t clampi(int32_t v, int32_t hi) { return v < 0 ? 0 : (v >= hi ? hi - 1 : v); }
-// A value known to be the same in every lane, moved to a scalar register (so
-// that the addresses and loops it controls are scalar too).
-__device__ __forceinline__ int32_t uni(int32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// Explicit address spaces for the hot loops, which live in non-inlined
-// functions (where pointers are generic): log A is never written during a
-// decode, so a wave-uniform pointer to it may be read through the constant
-// address space (scalar loads); per-lane data goes through the global one.
-typedef __attribute__((address_space(4))) const float cfloat_t;
-typedef __attribute__((address_space(1))) const float gfloat_t;
-__device__ __forceinline__ cfloat_t* uniform_const(const float* p) {
-    const uint64_t v = reinterpret_cast<uint64_t>(p);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-    return reinterpret_cast<cfloat_t*>(((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ gfloat_t* as_global(const float* p) {
-    return reinterpret_cast<gfloat_t*>(reinterpret_cast<uint64_t>(p));
-}
-// coherent (agent-scope) load through the global address space
-__device__ __forceinline__ float ld_cg(const float* p) {
-    typedef __attribute__((address_space(1))) const uint32_t gu32_t;
-    gu32_t* q = reinterpret_cast<gu32_t*>(reinterpret_cast<uint64_t>(p));
-    return __uint_as_float(__hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
-
-// Final arg-max keys are combined by tiles and read by the finalize step
-// with coherent loads, so the max is performed at the memory side (sc1).
-__device__ __forceinline__ void key_max(unsigned long long* p, unsigned long long v) {
-    __hip_atomic_fetch_max(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-}
-
-__device__ __forceinline__ uint32_t my_xcd() {
-    return __builtin_amdgcn_s_getreg((15 << 11) | (0 << 6) | 20) & (kXcd - 1);  // HW_REG_XCC_ID
-}
-
-__device__ __forceinline__ unsigned long long order_key(float v, int32_t j) {
-    if (v == 0.0f) v = 0.0f;  // -0 and +0 compare equal; the lower index must win
-    uint32_t b = __float_as_uint(v);
-    uint32_t o = (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-    return ((unsigned long long)o << 32) | (unsigned long long)(0xFFFFFFFFu - (uint32_t)j);
-}
-
-// Emission score of the Gaussian point model: state j's point xy[j] against
-// observation t's point obs[t], in float64 with each operation rounded once
-// (no contraction into fused multiply-adds), then rounded to float32:
-// (float)(c2 * ((x - u)^2 + (y - v)^2) - c0).
-__device__ __forceinline__ float gauss2d_score(const double* __restrict__ xy, const double* __restrict__ obs,
-                                               double c2, double c0, int32_t t, int32_t j) {
-#pragma clang fp contract(off)
-    const double dx = xy[2 * (int64_t)j] - obs[2 * (int64_t)t];
-    const double dy = xy[2 * (int64_t)j + 1] - obs[2 * (int64_t)t + 1];
-    const double sx = dx * dx;
-    const double sy = dy * dy;
-    const double d2 = sx + sy;
-    const double e = c2 * d2;
-    return (float)(e - c0);
-}
-
-// log B_t(j) of a sequence whose emission data starts at lb: its table's
-// entry lb[t * ld + j], or the Gaussian point model's score with lb
-// addressing the observations (float64 [T][2]).  emit_kind is uniform.
-__device__ __forceinline__ float emission_of(int32_t kind, const double* xy, double c2, double c0,
-                                             const float* __restrict__ lb, int64_t ld, int32_t t, int32_t j) {
-    if (kind == FV_EMIT_TABLE) return as_global(lb)[(int64_t)t * ld + j];
-    return gauss2d_score(xy, reinterpret_cast<const double*>(lb), c2, c0, t, j);
-}
-__device__ __forceinline__ float emission(cargs_t& a, const float* lb, int64_t ld, int32_t t, int32_t j) {
-    return emission_of(a.emit_kind, a.emit_xy, a.emit_c2, a.emit_c0, lb, ld, t, j);
-}
 
 __device__ __forceinline__ float* slot_delta(cargs_t& a, int32_t slot, int32_t parity) {
     return a.slot_base + (int64_t)slot * a.slot_floats + (int64_t)parity * a.Kp;
@@ -3673,6 +3551,7 @@ extern "C" __global__ __launch_bounds__(kEngBlock) void fv_engine_kernel(const E
     for (int32_t mi = 0; mi < n_models; ++mi) {
         __syncthreads();
         cargs_t& a = *reinterpret_cast<cargs_t*>(reinterpret_cast<uint64_t>(table + mi));
+        if (a.bounded && a.st->q_tail0 == 0) continue;   // nothing was left to the engine
         if (a.wide) engine_model<true, false>(a);
         else if (a.slab) engine_model<false, true>(a);
         else engine_model<false, false>(a);
@@ -4460,9 +4339,13 @@ extern "C" __global__ __launch_bounds__(kBlock) void fv_prep_dense_kernel(const 
 
 // At[j * Kp + i] = Ap[i * Kp + j]: the transposed (column-major) copy of the
 // padded log A, read by the two-column items' refine.  64 x 64 tiles through
-// LDS, 256 threads per tile; grid (Kp / 64, Kp / 64).
+// LDS, 256 threads per tile; grid (Kp / 64, Kp / 64).  Nothing is done when
+// `need` points to zero: the engine, which reads the copy, has nothing left to
+// decode.
 extern "C" __global__ __launch_bounds__(kBlock) void fv_transpose_dense_kernel(const float* __restrict__ Ap,
-                                                                               int32_t Kp, float* __restrict__ At) {
+                                                                               int32_t Kp, float* __restrict__ At,
+                                                                               const int32_t* __restrict__ need) {
+    if (need && *need == 0) return;
     __shared__ float tile[64][65];
     const int32_t i0 = blockIdx.y * 64, j0 = blockIdx.x * 64;
     const int32_t c = threadIdx.x & 63, r4 = threadIdx.x >> 6;
@@ -4519,6 +4402,8 @@ extern "C" __global__ __launch_bounds__(kBlock) void fv_setup_kernel(EngineArgs 
             si.psi_off = base[2] + scan[2][tid] - v[2];
             si.status = FV_OK;
             si.orig = b;
+            si.walked = 0;
+            si.pad = 0;
             a.seqs[li] = si;
             a.keys[li] = 0ull;
             if (si.T == 0 && d.score) *d.score = 0.0f;
@@ -4606,7 +4491,12 @@ extern "C" __global__ __launch_bounds__(kBlock) void fv_setup_kernel(EngineArgs 
     for (int32_t k = tid; k < (int32_t)(sizeof(EngineState) / 4); k += kBlock) words[k] = 0;
     for (int32_t k = tid; k < a.n_compute_blocks + 1; k += kBlock) a.arrive[k] = 0;
     __syncthreads();
-    if (tid == 0) st->q_tail0 = n_tasks;
+    if (a.bounded)
+        for (int32_t k = tid; k < a.K; k += kBlock) a.cmax[k] = 0;
+    if (tid == 0) {
+        st->q_tail0 = n_tasks;
+        st->bq_res = st->bq_pub = st->bq_live = (uint32_t)n_tasks;
+    }
 }
 
 // Sequences whose model index is outside [0, n_models) belong to no decode.
@@ -4632,7 +4522,7 @@ extern "C" __global__ __launch_bounds__(kBlock) void fv_finish_kernel(EngineArgs
     }
     if (a.bad_model && stv != FV_E_DEVICE && sq.T > 0 && sq.orig >= 0 && (*a.bad_model || a.bad_seq[sq.orig]))
         stv = FV_E_INVALID_ARG;
-    if (stv == FV_OK && a.method == FV_VANILLA && sq.T > 1 && !a.path_done) {
+    if (stv == FV_OK && a.method == FV_VANILLA && sq.T > 1 && !a.path_done && !sq.walked) {
         int32_t q = sq.path[sq.T - 1];
         const uint16_t* tab = a.psi16 + sq.psi_off;
         for (int32_t t = sq.T - 1; t > 0; --t) {

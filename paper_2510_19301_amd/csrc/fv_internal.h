@@ -75,6 +75,13 @@ constexpr int32_t kLeafMaxKp = 2048;   // larger K: no leaves (table too large p
 // in LDS and refine from a transposed copy of log A: up to this Kp.
 constexpr int32_t kColMaxKp = 4096;
 
+// Bounded decodes (fv_bound.hip): the largest K, groups of 64 columns a
+// block owns at most, blocks at most (one a CU), and the bound on any wait (each waits for a running block; far above any valid one).
+constexpr int32_t kBoundMaxK = 16384;
+constexpr int kTeamGroups = 16;
+constexpr int32_t kTeamBlocks = 256;
+constexpr int64_t kTeamSpin = (int64_t)1 << 28;
+
 // One vanilla decode of a dense model with K <= kSmallK runs on one wave
 // instead of the persistent engine.
 constexpr int32_t kSmallK = 256;
@@ -127,6 +134,8 @@ struct SeqInfo {
     int64_t psi_off;     // into the vanilla table, in entries
     int32_t status;
     int32_t orig;        // index of the sequence in the caller's array
+    int32_t walked;      // the decode kernel walked this sequence's backpointer table
+    int32_t pad;
 };
 
 // XCD-partitioned control block.  Buffer slot s belongs to XCD s % kXcd;
@@ -149,6 +158,10 @@ struct EngineState {
     uint32_t xcd_blocks[kXcd][kLine];  // compute blocks per XCD (counted at start)
     int32_t claim[2][kXcd][kLine];     // [parity][xcd] next unclaimed work unit of a step
     int32_t wclaim[2][kLine];          // [parity] next unclaimed wide item of a step
+    // bounded decode (fv_bound.hip): task tickets taken, queue entries
+    // reserved and published, tasks not finished, blocks that ended
+    uint32_t bq_head, bpad0[kLine - 1];
+    uint32_t bq_res, bq_pub, bq_live, bq_done, bpad1[kLine - 4];
     // a step's row counts of each XCD, tagged with the epoch of the barrier
     // that publishes them (see pack_counts), so that a block waiting at that
     // barrier receives them with its release flag
@@ -197,7 +210,7 @@ struct EngineArgs {
     int32_t leaf_len;           // subtasks of at most this many steps are leaves (0: none)
     int32_t beam_q;             // beam rows run four to a block (dense, one part, small K and B)
     int32_t relative_init;      // subtask starts drop the carried score (FV_FLAG_RELATIVE_INIT)
-    int32_t path_done;          // the decode kernel walked the vanilla table itself (finish skips it)
+    int32_t path_done;          // the decode kernel walked every vanilla table itself (finish skips it)
     int64_t leaf_off;           // floats from a slot's start to its leaf table
     // sparse transitions (CSR out-edges and their in-edge transpose in edge
     // order); null for dense models
@@ -233,6 +246,16 @@ struct EngineArgs {
     int32_t emit_kind;
     const double* emit_xy;      // [K][2] state points
     double emit_c2, emit_c0;    // log B_t(j) = (float)(c2 * d2 - c0)
+    // bounded decode (dense models, fv_bound.hip)
+    int32_t bounded;            // the decode started there: the engine takes what is left in the queue
+    int32_t b_leaf;             // segments of at most this many positions keep backpointers
+    int32_t b_split;            // longer ones are split into at most this many
+    uint32_t* cmax;             // [K] column maxima of log A as order keys
+    int32_t b_team;             // blocks of a team
+    char* bscr;                 // per-team scratch: division copies or a leaf's backpointers
+    int64_t bscr_bytes;
+    char* bxch;                 // per-team exchange buffers (zeroed)
+    int64_t bxch_bytes;
     // input validation (FV_FLAG_VALIDATE): null when not requested
     const int32_t* bad_seq;     // [caller's n_seqs] nonzero: NaN or +inf in that sequence's log B
     const int32_t* bad_model;   // nonzero: NaN or +inf in this model's log A or log pi
