@@ -23,12 +23,15 @@ extern "C" __global__ void fv_small_flash32_kernel(const EngineArgs* __restrict_
 extern "C" __global__ void fv_small_flash64_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_small_flash128_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_small_flash256_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_bound512_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_bound1k_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_team1k_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_team4k_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_team16k_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_colmax_kernel(const float* __restrict__ log_a, int32_t K, uint32_t* __restrict__ cmax,
                                             uint4* __restrict__ zero, int64_t nzero);
+extern "C" __global__ void fv_rowbound_kernel(const float* __restrict__ Ap, int32_t K, int32_t Kp,
+                                              const uint32_t* __restrict__ cmax, uint32_t* __restrict__ rowb);
 extern "C" __global__ void fv_fill_i32_kernel(int32_t* __restrict__ p, int64_t n, int32_t v);
 extern "C" __global__ void fv_validate_array_kernel(const float* __restrict__ p, int64_t n, int32_t* __restrict__ flag);
 extern "C" __global__ void fv_validate_points_kernel(const double* __restrict__ p, int64_t n, int32_t* flag);
@@ -117,8 +120,7 @@ constexpr int32_t kMaxSparseK = 1 << 30;
 constexpr int64_t kMaxNnz = 0x7fffffffLL;
 constexpr int32_t kMaxBlocks = 4096;    // engine grid size limit (arrival flags)
 constexpr int kEngineBlock = 1024;      // engine threads per block (one block per CU)
-constexpr int kTeamBlock = 1024;        // threads per block of a team,
-constexpr int kBoundBlock = 1024;       // of a single block's task
+constexpr int kTeamBlock = 1024;        // threads per block of a bounded decode
 
 struct Region {
     size_t off = 0, bytes = 0;
@@ -143,7 +145,7 @@ struct DenseLayout {
     int64_t n_segs = 0;          // first-level FLASH segments of at least two positions
     int32_t team = 0, teams = 0; // bounded decodes: blocks of a team, and teams (0: not bounded)
     int64_t xch_bytes = 0;       // a team's exchange buffer
-    Region cmax, xch;            // column maxima and exchange buffers of bounded decodes
+    Region cmax, rowb, xch;      // column maxima, row bounds and exchange buffers of bounded decodes
     int64_t leaf_tasks = 0;      // task-tree nodes when leaves end the bisection (slot sizing)
     Region Ap, At, seq1, seqinfo, keys, args, state, arrive, rows_full, rows_light, rows_beam, queue, free_stack,
         slots, alpha, root, psi, csr_flag, csr_ptr, csr_deg, csr_eid, csr_src, csr_val;
@@ -173,6 +175,12 @@ size_t put(size_t& cur, Region& r, size_t bytes) {
     r.bytes = bytes;
     cur = r.off + bytes;
     return r.off;
+}
+
+// Which of the bounded kernels decodes K states on teams of `team` blocks
+int team_kernel(int32_t K, int32_t team) {
+    if (team == 1) return K <= 512 ? 0 : 1;
+    return K <= 1024 ? 2 : (K <= 4096 ? 3 : 4);
 }
 
 // Workspace layout of a dense decode.  Depends only on the arguments, so
@@ -326,6 +334,7 @@ fv_status plan_dense(int32_t method, const fv_trans* A, const int32_t* T_host, i
         L.xch_bytes = round_up(((L.team > 1 ? 2 * (int64_t)L.Kp + 2 * round_up(groups, 16) : 0) + 16 + L.team) * 8, kAlign);
     }
     put(cur, L.cmax, L.teams ? (size_t)K * 4 : 0);
+    put(cur, L.rowb, L.teams && team_kernel(K, L.team) == 1 ? (size_t)L.Kp * (L.Kp / 64) * 4 : 0);
     // (as many as can be resident, so that the size does not grow with P)
     put(cur, L.xch, (size_t)(method == FV_FLASH && L.team ? kTeamBlocks / L.team : L.teams) * L.xch_bytes);
     put(cur, L.seq1, single ? sizeof(fv_seq) : 0);
@@ -399,7 +408,7 @@ void launch_transpose(const fv_trans* A, const DenseLayout& L, char* w, hipStrea
 struct DeviceInfo {
     int cus = 0;
     int engine_blocks_per_cu = 0;
-    int team_blocks_per_cu[4] = {0, 0, 0, 0};   // one block, K <= 1024, 4096, 16384
+    int team_blocks_per_cu[5] = {0, 0, 0, 0, 0};   // one block K <= 512, 1024; teams K <= 1024, 4096, 16384
 };
 
 // Queried once per device and cached: a decode call then does no property
@@ -442,13 +451,13 @@ fv_status device_info(DeviceInfo& di) {
         HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(fv_engine_kernel),
                                                              kEngineBlock, 0));
         d.engine_blocks_per_cu = nb;
-        const void* const team[4] = {reinterpret_cast<const void*>(fv_bound1k_kernel),
+        const void* const team[5] = {reinterpret_cast<const void*>(fv_bound512_kernel),
+                                     reinterpret_cast<const void*>(fv_bound1k_kernel),
                                      reinterpret_cast<const void*>(fv_team1k_kernel),
                                      reinterpret_cast<const void*>(fv_team4k_kernel),
                                      reinterpret_cast<const void*>(fv_team16k_kernel)};
-        for (int k = 0; k < 4; ++k)
-            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&d.team_blocks_per_cu[k], team[k],
-                                                                 k == 0 ? kBoundBlock : kTeamBlock, 0));
+        for (int k = 0; k < 5; ++k)
+            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&d.team_blocks_per_cu[k], team[k], kTeamBlock, 0));
         if (nb < 1) return fail(FV_E_DEVICE, "engine kernel cannot be resident");
         g_dev_info[dev] = d;
         g_dev_known[dev] = true;
@@ -482,7 +491,7 @@ BoundPlan plan_bounded(uint32_t flags, int32_t method, const fv_trans* A, const 
     // the engine's own hooks, mean the lock-step engine
     if (!L.teams || (flags & ~(uint32_t)FV_FLAG_VALIDATE) || g_dbg_max_steps || g_dbg_spin_limit || g_dbg_trace) return b;
     // the blocks of the teams wait for each other: all of them are resident
-    const int32_t resident = di.cus * di.team_blocks_per_cu[L.team == 1 ? 0 : (A->K <= 1024 ? 1 : (A->K <= 4096 ? 2 : 3))];
+    const int32_t resident = di.cus * di.team_blocks_per_cu[team_kernel(A->K, L.team)];
     if (resident < L.team) return b;
     b.teams = std::min(L.teams, resident / L.team);
     if (method == FV_FLASH) {
@@ -796,6 +805,7 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
             a.b_split = bnd.split;
             a.b_team = L.team;
             a.cmax = static_cast<uint32_t*>(at(L.cmax));
+            a.rowb = static_cast<uint32_t*>(at(L.rowb));
             a.bscr = reinterpret_cast<char*>(a.slot_base);
             a.bscr_bytes = bnd.scratch;
             a.bxch = static_cast<char*>(at(L.xch));
@@ -830,6 +840,9 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
             hipLaunchKernelGGL(fv_colmax_kernel, dim3(chunks, std::max(1, std::min(A->K / 32, 512 / chunks))),
                                dim3(kBlock), 0, stream, A->log_a, A->K, a.cmax, reinterpret_cast<uint4*>(a.bxch),
                                (int64_t)bnd.teams * L.xch_bytes / 16);
+            if (L.rowb.bytes)
+                hipLaunchKernelGGL(fv_rowbound_kernel, dim3(L.Kp / 64, L.Kp / 64), dim3(kBlock), 0, stream, Ap, A->K, L.Kp,
+                               (const uint32_t*)a.cmax, a.rowb);
         }
     }
     if (status && !single && n_models > 1)
@@ -865,12 +878,14 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         const EngineArgs* ta = table_dev + p;
         void* targs[] = {&ta};
         const dim3 grid(bounds[p].teams * bp.L[p].team);
-        const void* const fn = bp.L[p].team == 1 ? reinterpret_cast<const void*>(fv_bound1k_kernel)
-                               : K <= 1024       ? reinterpret_cast<const void*>(fv_team1k_kernel)
-                               : K <= 4096       ? reinterpret_cast<const void*>(fv_team4k_kernel)
-                                                 : reinterpret_cast<const void*>(fv_team16k_kernel);
+        const void* const team[5] = {reinterpret_cast<const void*>(fv_bound512_kernel),
+                                     reinterpret_cast<const void*>(fv_bound1k_kernel),
+                                     reinterpret_cast<const void*>(fv_team1k_kernel),
+                                     reinterpret_cast<const void*>(fv_team4k_kernel),
+                                     reinterpret_cast<const void*>(fv_team16k_kernel)};
+        const void* const fn = team[team_kernel(K, bp.L[p].team)];
         if (bp.L[p].team > 1) HIP_TRY(hipLaunchCooperativeKernel(fn, grid, dim3(kTeamBlock), targs, 0, stream));
-        else HIP_TRY(hipLaunchKernel(fn, grid, dim3(kBoundBlock), targs, 0, stream));
+        else HIP_TRY(hipLaunchKernel(fn, grid, dim3(kTeamBlock), targs, 0, stream));
         if (bounds[p].rows > 0 && args[p].At)
             hipLaunchKernelGGL(fv_transpose_dense_kernel, dim3(args[p].Kp / 64, args[p].Kp / 64), dim3(kBlock), 0,
                                stream, args[p].Acol, args[p].Kp, const_cast<float*>(args[p].At), &args[p].st->q_tail0);

@@ -17,6 +17,20 @@
 // needed.  States below the last list are scanned only when the bound still
 // calls for them.
 //
+// FILTER: a wave with its own group (as many sequences as CUs, K > 512) is
+// bound by the log A rows it reads from L2 and by the two instructions a
+// candidate takes, so it first drops listed states by a closer bound: with
+// r_i = max_{j in H} (log A(i, j) - cm_j) over a half group H of 32 columns
+// (rounded up to float16; in LDS), delta_i + log A(i, j) <= (delta_i + r_i) +
+// cm_j, and states with fl(delta_i + r_i) < h lose where fl(h + cm_j) <
+// best_j.  h follows what the half group's last steps needed; where the
+// results do not close the bound it takes h from them and reads the rest,
+// once.  Of K = 1024 with Dirichlet(0.1) transitions a half group then reads
+// about 65 rows of 128 bytes instead of 200 of 256: 256 sequences, T ~ U[500,
+// 8000], FLASH P = 64: 111.5 -> 88.3 ms.  Where several waves share a group
+// (teams) the filter's own steps take longer than the rows it saves (K = 512,
+// one sequence: 2.0 -> 2.6 ms; 64 sequences of K = 1000: 13.3 -> 17.3 ms).
+//
 // Work division.  A team of M blocks decodes one task (a vanilla pass, a FLASH
 // root, a FLASH segment); each block owns up to kTeamGroups groups of 64
 // columns.  After a step each group's wave publishes its scores as 64-bit
@@ -32,7 +46,7 @@
 // Measured against the lock-step engine (a global step of 15 to 28 us for all
 // rows): K = 512 Erdos-Renyi graph, T = 512, FLASH P = 16: 7.1 -> 2.0 ms; 64
 // sequences, K = 1000, T ~ U[100, 2000], vanilla: 34.6 -> 13.3 ms; 256
-// sequences, K = 1024, T ~ U[500, 8000], FLASH P = 64: 244 -> 112 ms;
+// sequences, K = 1024, T ~ U[500, 8000], FLASH P = 64: 244 -> 112 (now 88) ms;
 // K = 16384, T = 512, vanilla: 102 -> 24.5 ms; K = 5001, T = 777, FLASH
 // P = 16: 39.3 -> 16.7 ms.
 #include <float.h>
@@ -42,8 +56,14 @@
 namespace fv {
 
 constexpr int kTiers = 3;
+// FILTER: reach of the near and the far list in distances that the block's
+// groups needed, of h in those that the half group needed, and the weight of
+// a new one (swept: 1.0 / 1.6 / 1.1 / 0.3 takes 2% longer, h at 0.9 needs the
+// second reading in 78% instead of 35% of the steps and takes 20% longer)
+constexpr float kNear = 0.9f, kFar = 1.4f, kHalf = 1.15f, kEma = 0.2f;
 constexpr int32_t kBoundRetry = 77;   // sequence status: left to the lock-step engine
 constexpr int kTCols = 64 * kTeamGroups;   // columns of a block, at most
+constexpr int kRowCap = 128;          // rows of a wave's lists (FILTER)
 constexpr int kUnit = 8;              // list entries of a unit of work
 constexpr int kUnitLoads = kUnit / 4; // 16 lanes across 64 columns: 4 entries side by side
 
@@ -65,16 +85,18 @@ struct BoundEnt {
 // wave complete in order, so an emission load in flight holds back every
 // log A row read after it for as long as HBM takes; in groups of NB rows that
 // wait comes once every NB steps.)
-template <int KC, int LC, int NB, bool TEAM>
+template <int KC, int LC, int NB, bool TEAM, bool FILTER>
 struct TeamLds {
     union {
         struct {
-            BoundEnt list[kTiers][LC];      // scanned states, unordered
+            BoundEnt list[FILTER ? 1 : kTiers][LC];   // scanned states, unordered
+            BoundEnt rows[FILTER ? 16 : 1][2][FILTER ? kRowCap + 16 : 1];   // a wave's rows to read, by half of its group
             float eb[2][NB * kTCols];       // emission rows of the block's columns: in use, and coming
         };
-        uint32_t walk[(8 * kTiers * LC + 8 * NB * kTCols) / 4];   // backpointer rows being walked
+        uint32_t walk[(8 * (FILTER ? 1 : kTiers) * LC + (FILTER ? 256 * (kRowCap + 16) : 16) + 8 * NB * kTCols) / 4];   // backpointer rows being walked
     };
-    unsigned long long part[kTCols];   // order keys of partial maxima
+    unsigned long long part[FILTER ? 1 : kTCols];   // order keys of partial maxima
+    uint32_t rb[FILTER ? 16 * KC : 1];   // [groups, Kp] row bounds of both halves
     float cm[kTCols];                  // column maxima; NaN where no scan is ever needed
     uint16_t pb[2][NB * kTCols];       // backpointer rows: being made, being stored
     uint16_t anc[TEAM ? 1 : 2][KC];    // tracked division state of every state
@@ -100,6 +122,12 @@ __device__ __forceinline__ uint32_t wave_max(uint32_t v) {   // in every lane
     v = max(v, dpp_u<0x143, 0xc>(v));   // row_bcast:31
     return (uint32_t)__builtin_amdgcn_readlane((int32_t)v, 63);
 }
+// v, hidden from the compiler: addresses made from it are formed where they are
+// used, not kept in registers across the steps
+__device__ __forceinline__ int32_t fresh(int32_t v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
 // fmax would first quiet its operands, a second instruction for each
 __device__ __forceinline__ double max64(double a, double b) {
     double r;
@@ -121,6 +149,38 @@ __device__ __forceinline__ double swap_max16(double a, double b) {   // even row
 // ends with column 4 (lane mod 16) + r.
 __device__ __forceinline__ double merge_group(const double (&b)[4]) {
     return swap_max16(swap_max32(b[0], b[2]), swap_max32(b[1], b[3]));
+}
+// The same for two half groups of 32 columns (lanes equal modulo 8 scanned the
+// same four columns of either): lane l ends with column 4 (l mod 8) + l / 16 of
+// half (l / 8) mod 2.
+__device__ __forceinline__ double merge_halves(const double (&b0)[4], const double (&b1)[4]) {
+    const double m0 = merge_group(b0), m1 = merge_group(b1);
+    const bool up = threadIdx.x & 8;
+    const double keep = up ? m1 : m0, give = up ? m0 : m1;
+    const int32_t lo = __builtin_amdgcn_update_dpp(0, __double2loint(give), 0x128, 0xf, 0xf, false);   // row_ror:8
+    const int32_t hi = __builtin_amdgcn_update_dpp(0, __double2hiint(give), 0x128, 0xf, 0xf, false);
+    return max64(keep, __hiloint2double(hi, lo));
+}
+// largest of the lanes of a half (lanes with equal bit 3), in each of them
+__device__ __forceinline__ uint32_t half_max(uint32_t v) {
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, 0xb1, 0xf, 0xf, false));    // quad_perm: 1, 0, 3, 2
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, 0x4e, 0xf, 0xf, false));    // quad_perm: 2, 3, 0, 1
+    v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, 0x141, 0xf, 0xf, false));   // row_half_mirror
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = max((uint32_t)a[0], (uint32_t)a[1]);
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return max((uint32_t)b[0], (uint32_t)b[1]);
+}
+// x + the float16 in the low (high) half of r
+__device__ __forceinline__ float add_lo16(float x, uint32_t r) {
+    float s;
+    asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(s) : "v"(r), "v"(x));
+    return s;
+}
+__device__ __forceinline__ float add_hi16(float x, uint32_t r) {
+    float s;
+    asm("v_fma_mix_f32 %0, %1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(s) : "v"(r), "v"(x));
+    return s;
 }
 __device__ __forceinline__ uint32_t score_key(float v) {
     const uint32_t b = __float_as_uint(v);
@@ -176,13 +236,13 @@ __device__ __forceinline__ unsigned long long team_word(float v, uint32_t mid, u
 enum : int32_t { BM_VANILLA = 0, BM_DIV = 1, BM_LEAF = 2 };
 
 // W: waves of a block.
-template <int KC, int LC, int NB, bool TEAM, int W>
+template <int KC, int LC, int NB, bool TEAM, int W, bool FILTER>
 __device__ __forceinline__ void team_decode(cargs_t& a) {
     constexpr int kTThreads = 64 * W;
-    constexpr int GPW = TEAM ? kTeamGroups / W : (KC / 64 + W - 1) / W;   // groups of a wave, at most
+    constexpr int GPW = 1;   // groups of a wave, at most
     // long rows: the groups' maxima are polled first, the words then read once
     constexpr bool GATE = TEAM && KC > 4096;
-    __shared__ __align__(16) TeamLds<KC, LC, NB, TEAM> s;
+    __shared__ __align__(16) TeamLds<KC, LC, NB, TEAM, FILTER> s;
     const int32_t tid = threadIdx.x, lane = tid & 63, wv = uni(tid >> 6);
     const int32_t K = a.K, Kp = a.Kp, M = a.b_team;
     if (Kp > KC) return;
@@ -202,23 +262,28 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
     // waves of a group: all of them for a single group, ..., one where there
     // are more groups than half the waves
     int32_t wpg = W;
+    if (FILTER) wpg = 1;
     while (wpg > 1 && wpg * ngl > W) wpg >>= 1;
     const int32_t g0 = wv / wpg, sub = wv - g0 * wpg;             // this wave's (first) group and share of it
     const int32_t lc4 = 4 * (lane & 15);
     int32_t g = g0;                                               // the group being worked on, and
-    int32_t jl = g * 64 + lc4 + (lane >> 4);                      // the column (in the block) a lane ends with
+    // the column (in the block) a lane ends with
+    int32_t jl = g * 64 + (FILTER ? 4 * (lane & 8) + 4 * (lane & 7) : lc4) + (lane >> 4);
     bool active = g < ngl;
     auto at_group = [&](int32_t k) {                              // this wave's k-th group
         g = g0 + k * W;
-        jl = g * 64 + lc4 + (lane >> 4);
+        if (!FILTER) jl = g * 64 + lc4 + (lane >> 4);
         active = g < ngl;
     };
     for (int32_t k = tid; k < kTCols; k += kTThreads) {
         const float c = k < cn ? score_of_key(a.cmax[cb + k]) : -INFINITY;
         s.cm[k] = c > -INFINITY ? c : __builtin_nanf("");
     }
+    if constexpr (FILTER)
+        for (int32_t k = tid; k < ngl * Kp; k += kTThreads) s.rb[k] = a.rowb[k];
     const double none = __hiloint2double((int32_t)0xff800000u, 0);
     float G = 8.0f, G1 = 16.0f;   // distance below the maximum that the scans are expected to need
+    float F = 8.0f, F1 = 16.0f;   // and (FILTER) those of the lane's half group
     uint32_t epoch = 1;        // tag of the scores of a task's first position
     unsigned long long task_no = 0;
     for (;;) {
@@ -480,9 +545,9 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             float h0, h1, h2;
             for (int32_t go = 0;; ++go) {
             const float gx = (step == 0 ? G1 : G) * __int_as_float((127 - go) << 23);
-            h0 = D - (wpg > 1 ? 1.0f : 0.75f) * gx;
-            h1 = D - (wpg > 1 ? 1.2f : 1.0f) * gx;
-            h2 = D - (GATE ? 1.4f : (wpg > 1 ? 1.7f : 1.35f)) * gx;
+            h0 = D - (FILTER ? kNear : (wpg > 1 ? 1.0f : 0.75f)) * gx;
+            h1 = D - (FILTER ? kFar : (wpg > 1 ? 1.2f : 1.0f)) * gx;
+            h2 = FILTER ? h1 : D - (GATE ? 1.4f : (wpg > 1 ? 1.7f : 1.35f)) * gx;
 #pragma unroll
             for (int c = 0; c < NS; c += CN) {
                 if (c * kTThreads >= K) break;
@@ -523,7 +588,8 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                                         __builtin_amdgcn_mbcnt_hi((uint32_t)(my >> 32),
                                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)my, 0));
                     if (fin && x[k] >= h2 && (LC >= KC || pos < LC))
-                        s.list[l][pos] = BoundEnt{(tid + (c + k) * kTThreads) ^ flip, x[k]};
+                        s.list[FILTER ? 0 : l][FILTER && l ? LC - 1 - pos : pos] =
+                            BoundEnt{(tid + (c + k) * kTThreads) ^ flip, x[k]};
                 }
             }
             if (LC >= KC || go == 8) break;
@@ -553,6 +619,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             // complete lists, and whether any finite score lies below them
             int32_t lists = kTiers;
             const int4 cn4 = *reinterpret_cast<const int4*>(s.cnt[par]);
+            if constexpr (FILTER) lists = 2;
             if constexpr (LC < KC) lists = uni(cn4.x) > LC ? 0 : (uni(cn4.y) > LC ? 1 : (uni(cn4.z) > LC ? 2 : 3));
             const bool outside = uni(cn4.w) != 0 || lists < kTiers;
             // above every score outside the first n lists
@@ -582,10 +649,57 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 if constexpr (TEAM) return __uint_as_float((uint32_t)ld_c(tb.x[xp] + i));
                 else return s.x[xp][i];
             };
-            // the result of this wave's group from its first `done` lists and, out,
-            // the best (fo, qo) of the states outside them: the sign check, the
-            // score, the state and the division state
-            auto finish = [&](double top, int32_t done, bool out, float fo, int32_t qo) {
+            // the best candidate of this lane's column among the states that score
+            // from thr up to (not including) top_of
+            auto scan_states = [&](float thr, float top_of, float& f, int32_t& q) {
+                f = -INFINITY;
+                q = 0;
+                gfloat_t* const ak = as_global(a.Acol) + fresh(cb + jl);
+#pragma unroll 1
+                for (int32_t c0 = 0; c0 < K; c0 += 256) {
+                    float xo[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) xo[u] = score_at(min(c0 + u * 64 + fresh(lane), K - 1));
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const bool in = c0 + u * 64 + lane < K && xo[u] >= thr && xo[u] < top_of && xo[u] > -INFINITY;
+                        uint64_t mask = __builtin_amdgcn_ballot_w64(in);
+                        while (mask) {   // four rows in flight
+                            int32_t r[4];
+                            float v[4];
+#pragma unroll
+                            for (int w = 0; w < 4; ++w) {
+                                r[w] = mask ? (int32_t)__builtin_ctzll(mask) : r[w ? w - 1 : 0];
+                                mask &= mask - 1;
+                                v[w] = ak[(uint32_t)(c0 + u * 64 + r[w]) * (uint32_t)Kp];
+                            }
+#pragma unroll
+                            for (int w = 0; w < 4; ++w)
+                                take1(f, q, __int_as_float(__builtin_amdgcn_readlane(__float_as_int(xo[u]), r[w])) + v[w],
+                                      c0 + u * 64 + r[w]);
+                        }
+                    }
+                }
+            };
+            // the maxima top, of the states that score from thr on, with those below:
+            // thr becomes a score below which none can win (checked, not derived: the
+            // subtraction is rounded)
+            auto beyond = [&](double top, float& thr) {
+                const float bs = __int_as_float(__double2hiint(top)), cm = s.cm[jl], top_of = thr;
+                const float nd = D - (bs - cm);
+                const float lim = __uint_as_float(wave_max(nd > 0.0f ? __float_as_uint(nd) : 0u));
+                thr = D - lim * 1.001f - 1e-6f * fabsf(D);
+                if (__builtin_amdgcn_ballot_w64(cm == cm && !(thr + cm < bs))) thr = -FLT_MAX;
+                float f;
+                int32_t q;
+                scan_states(thr, top_of, f, q);
+                return max64(top, __hiloint2double(__float_as_int(f), q ^ flip));
+            };
+            // the result of this wave's group: the sign check, the score, the state
+            // and the division state.  Scanned were (FILTER) the states from thr on
+            // that may win, or the first `done` lists and, out, the states outside
+            // them, whose best is fo of qo.
+            auto finish = [&](double top, float thr, int32_t done, bool out, float fo, int32_t qo) {
                 // scores of the other sign, or zeros, where the low word does not
                 // order equal candidates: compare by value and state
                 const float b0 = __int_as_float(__double2hiint(top));
@@ -593,21 +707,25 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 if (__builtin_amdgcn_ballot_w64(odd)) {
                     float f = -INFINITY;
                     int32_t q = 0;
-                    gfloat_t* const ak = as_global(a.Acol) + cb + jl;
-                    for (int32_t l = 0; l < done; ++l) {
-                        const int32_t cnt = uni(s.cnt[par][l]);
-                        for (int32_t p = 0; p < cnt; p += 8) {
-                            BoundEnt en[8];
-                            float v[8];
-#pragma unroll
-                            for (int u = 0; u < 8; ++u) en[u] = s.list[l][min(p + u, cnt - 1)];
-#pragma unroll
-                            for (int u = 0; u < 8; ++u) v[u] = ak[(uint32_t)(en[u].lo ^ flip) * (uint32_t)Kp];
-#pragma unroll
-                            for (int u = 0; u < 8; ++u) take1(f, q, en[u].v + v[u], en[u].lo ^ flip);
+                    if constexpr (FILTER) {
+                        scan_states(thr, INFINITY, f, q);
+                    } else {
+                        gfloat_t* const ak = as_global(a.Acol) + cb + jl;
+                        for (int32_t l = 0; l < done; ++l) {
+                            const int32_t cnt = uni(s.cnt[par][l]);
+                            for (int32_t p = 0; p < cnt; p += 8) {
+                                BoundEnt en[8];
+                                float v[8];
+    #pragma unroll
+                                for (int u = 0; u < 8; ++u) en[u] = s.list[l][min(p + u, cnt - 1)];
+    #pragma unroll
+                                for (int u = 0; u < 8; ++u) v[u] = ak[(uint32_t)(en[u].lo ^ flip) * (uint32_t)Kp];
+    #pragma unroll
+                                for (int u = 0; u < 8; ++u) take1(f, q, en[u].v + v[u], en[u].lo ^ flip);
+                            }
                         }
+                        if (out) take1(f, q, fo, qo);
                     }
-                    if (out) take1(f, q, fo, qo);
                     top = __hiloint2double(__float_as_int(f), q ^ flip);
                 }
                 const float b = __int_as_float(__double2hiint(top));
@@ -635,6 +753,136 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                         give_up = ld_c(tb.beyond) > (unsigned long long)ngt * (unsigned long long)(8 + step / 8) ? 1u : 0u;
                 }
             };
+            if constexpr (FILTER) {
+                if (active) {
+                    double b0[4] = {none, none, none, none}, b1[4] = {none, none, none, none};
+                    const int32_t add = (g * 64 + 4 * (lane & 7)) * 4 + add0;
+                    // rows of a half's list: 8 lanes across 32 columns, 8 rows a load
+                    auto fetch_rows = [&](auto& en, auto& av, int32_t hf, int32_t at) {
+                        constexpr int N = sizeof(en) / sizeof(en[0]);
+#pragma unroll
+                        for (int u = 0; u < N; ++u) en[u] = s.rows[wv][hf][at + (lane >> 3) + u * 8];
+#pragma unroll
+                        for (int u = 0; u < N; ++u)
+                            av[u] = *reinterpret_cast<gvec_t*>(A + (uint32_t)(__mul24(en[u].lo, mul) + add + hf * 128));
+                        __builtin_amdgcn_sched_barrier(0);   // every load is issued before the next wait
+                    };
+                    // both halves' lists: each half's next rows are in flight while the
+                    // other's are scanned
+                    auto scan_rows = [&](int32_t n0, int32_t n1) {
+                        constexpr int U = 2, inc = 8 * U;
+                        BoundEnt e0[U], e1[U];
+                        vec_t v0[U], v1[U];
+                        const int32_t most = max(n0, n1);
+                        // both lists to a multiple of 16 at the longer one's end: rows that cannot win
+                        for (int32_t e = min(n0, n1) + (lane & 15); e < most + 16; e += 16) {
+                            if (e >= n0) s.rows[wv][0][e] = BoundEnt{flip, -INFINITY};
+                            if (e >= n1) s.rows[wv][1][e] = BoundEnt{flip, -INFINITY};
+                        }
+                        fetch_rows(e0, v0, 0, 0);
+                        fetch_rows(e1, v1, 1, 0);
+#pragma unroll 1
+                        for (int32_t e = inc; e < most; e += inc) {
+                            scan(b0, e0, v0);
+                            fetch_rows(e0, v0, 0, e);
+                            scan(b1, e1, v1);
+                            fetch_rows(e1, v1, 1, e);
+                        }
+                        scan(b0, e0, v0);
+                        scan(b1, e1, v1);
+                    };
+                    const uint32_t* const rb = s.rb + g * Kp;
+                    // listed states with bounds from the lane's lo up to (not including) its hi
+                    auto filter = [&](float lo, float hi, int32_t tiers) {
+                        const float lo0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lo), 0));
+                        const float lo1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lo), 8));
+                        const float hi0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(hi), 0));
+                        const float hi1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(hi), 8));
+                        // near states from the list's front, far ones from its back
+                        const int32_t near = uni(cn4.x), listed = near + (tiers > 1 ? uni(cn4.y) : 0);
+                        int32_t n0 = 0, n1 = 0;
+#pragma unroll 1
+                        for (int32_t e = 0; e < listed; e += 256) {
+                            BoundEnt en[4];
+                            uint32_t r[4];
+                            float x[4];
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                const int32_t p = min(e + c * 64 + lane, listed - 1);
+                                en[c] = s.list[0][p < near ? p : LC - 1 - (p - near)];
+                            }
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) r[c] = rb[en[c].lo ^ flip];
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) x[c] = e + c * 64 + lane < listed ? en[c].v : -INFINITY;
+                            int32_t from = 0;   // 64s that are on the lists
+#pragma unroll 1
+                            do {
+                                bool room = true;
+#pragma unroll
+                                for (int c = 0; c < 4; ++c) {
+                                    if (c < from || !room) continue;
+                                    const float y0 = add_lo16(x[c], r[c]), y1 = add_hi16(x[c], r[c]);
+                                    const uint64_t m0 = __builtin_amdgcn_ballot_w64(y0 >= lo0) & __builtin_amdgcn_ballot_w64(y0 < hi0);
+                                    const uint64_t m1 = __builtin_amdgcn_ballot_w64(y1 >= lo1) & __builtin_amdgcn_ballot_w64(y1 < hi1);
+                                    const int32_t a0 = n0 + __popcll(m0), a1 = n1 + __popcll(m1);
+                                    room = max(a0, a1) <= kRowCap;
+                                    if (!room) continue;
+                                    if (y0 >= lo0 && y0 < hi0)
+                                        s.rows[wv][0][__builtin_amdgcn_mbcnt_hi((uint32_t)(m0 >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m0, n0))] = en[c];
+                                    if (y1 >= lo1 && y1 < hi1)
+                                        s.rows[wv][1][__builtin_amdgcn_mbcnt_hi((uint32_t)(m1 >> 32),
+                                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m1, n1))] = en[c];
+                                    n0 = a0;
+                                    n1 = a1;
+                                    from = c + 1;
+                                }
+                                if ((from < 4 || e + 256 >= listed) && max(n0, n1) > 0) {
+                                    scan_rows(n0, n1);
+                                    n0 = n1 = 0;
+                                }
+                            } while (from < 4);
+                        }
+                    };
+                    const float cm = s.cm[jl];
+                    // the distance that the columns of the lane's half need
+                    auto reach = [&](double top) {
+                        const float nd = D - (__int_as_float(__double2hiint(top)) - cm);   // NaN where nothing is needed
+                        return __uint_as_float(half_max(nd > 0.0f && nd < INFINITY ? __float_as_uint(nd) : 0u));
+                    };
+                    auto open = [&](float lo, double top) {
+                        return __builtin_amdgcn_ballot_w64(lo + cm >= __int_as_float(__double2hiint(top))) != 0;
+                    };
+                    float lo = fmaxf(h0, D - kHalf * (step == 0 ? F1 : F)), hi = INFINITY;
+                    double top;
+                    float u;
+                    bool more = false;
+#pragma unroll 1
+                    for (int round = 0;; ++round) {
+                        filter(lo, hi, __builtin_amdgcn_ballot_w64(lo < h0) ? 2 : 1);
+                        top = merge_halves(b0, b1);
+                        more = open(lo, top);
+                        u = reach(top);
+                        if (!more || round == 1) break;
+                        // no row whose bound is below the next lo can win (checked, not derived)
+                        hi = lo;
+                        lo = fminf(lo, D - u * 1.001f - 1e-6f * fabsf(D));
+                        const bool bad = cm == cm && !(lo + cm < __int_as_float(__double2hiint(top)));
+                        if (half_max(bad ? 1u : 0u) || lo < h1) lo = h1;
+                    }
+                    float thr = fminf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(lo), 0)),
+                                      __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lo), 8)));
+                    if (more && outside) {
+                        thr = h1;
+                        top = beyond(top, thr);
+                        u = reach(top);
+                    }
+                    if (step == 0) F1 = fmaxf(F1 + 0.5f * (u - F1), 1e-4f);
+                    else F = fmaxf(F + kEma * (u - F), 1e-4f);
+                    finish(top, thr, 0, more, 0.0f, 0);
+                }
+            } else
 #pragma unroll 1
             for (int gi = 0; gi < GPW; ++gi) {
             if (GPW > 1) {
@@ -738,7 +986,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     }
                     top = max64(top, __hiloint2double(__float_as_int(fo), qo ^ flip));
                 }
-                finish(top, k, out, fo, qo);
+                finish(top, 0.0f, k, out, fo, qo);
             }
             if (wpg > 1) break;
             }
@@ -931,19 +1179,52 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
     if (lane == 0) st->q_tail0 = left;
 }
 
-// One block per task for K <= 1024, teams for K <= 1024, 4096 and 16384; a
-// block takes a CU's 16 wavefronts (two blocks of 8 for one task each: 158
-// instead of 112 ms for 256 sequences of K = 1024, T ~ U[500, 8000], FLASH
-// P = 64, whose roots then leave half of them idle).
-#define FV_TEAM(NAME, KC, LC, NB, TEAM, W)                                                                    \
-    extern "C" __global__ __launch_bounds__(64 * W, 4) void NAME(const EngineArgs* __restrict__ table) {       \
-        team_decode<KC, LC, NB, TEAM, W>(*reinterpret_cast<cargs_t*>(reinterpret_cast<uint64_t>(table)));     \
+// One block per task for K <= 512 and 1024, teams for K <= 1024, 4096 and
+// 16384; a block takes a CU's 16 wavefronts (two blocks of 8 for one task
+// each: 158 instead of 112 ms for 256 sequences of K = 1024, FLASH P = 64, whose
+// roots then leave half of them idle).
+#define FV_TEAM(NAME, KC, LC, NB, TEAM, FILTER)                                                                 \
+    extern "C" __global__ __launch_bounds__(1024, 4) void NAME(const EngineArgs* __restrict__ table) {           \
+        team_decode<KC, LC, NB, TEAM, 16, FILTER>(*reinterpret_cast<cargs_t*>(reinterpret_cast<uint64_t>(table))); \
     }
-FV_TEAM(fv_bound1k_kernel, 1024, 1024, 4, false, 16)
-FV_TEAM(fv_team1k_kernel, 1024, 1024, 4, true, 16)
-FV_TEAM(fv_team4k_kernel, 4096, 2048, 4, true, 16)
-FV_TEAM(fv_team16k_kernel, 16384, 2048, 2, true, 16)
+FV_TEAM(fv_bound512_kernel, 1024, 1024, 4, false, false)
+FV_TEAM(fv_bound1k_kernel, 1024, 1024, 2, false, true)
+FV_TEAM(fv_team1k_kernel, 1024, 1024, 4, true, false)
+FV_TEAM(fv_team4k_kernel, 4096, 2048, 4, true, false)
+FV_TEAM(fv_team16k_kernel, 16384, 2048, 2, true, false)
 #undef FV_TEAM
+
+// Row bounds: rowb[g][i] (two float16) >= max over the 32 columns of either half
+// of group g of log A(i, j) - (column j's maximum); -inf where no column has an
+// edge from i.
+// A block takes 64 rows of a group.
+extern "C" __global__ __launch_bounds__(kBlock) void fv_rowbound_kernel(const float* __restrict__ Ap, int32_t K,
+                                                                        int32_t Kp,
+                                                                        const uint32_t* __restrict__ cmax,
+                                                                        uint32_t* __restrict__ rowb) {
+    __shared__ float part[64][65];
+    const int32_t c = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int32_t j = blockIdx.x * 64 + c, i0 = blockIdx.y * 64;
+    const float cm = j < K ? score_of_key(cmax[j]) : -INFINITY;
+    for (int32_t r = w; r < 64; r += kWaves) {
+        const int32_t i = i0 + r;
+        float v = -INFINITY;
+        // rounded towards zero, that is, up: the difference is not positive
+        if (i < K && cm > -INFINITY) v = (Ap[(int64_t)i * Kp + j] - cm) * (1.0f - 0x1p-20f);
+        part[r][c] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        const int32_t r = threadIdx.x;
+        float v0 = -INFINITY, v1 = -INFINITY;
+#pragma unroll
+        for (int k = 0; k < 32; ++k) {
+            v0 = fmaxf(v0, part[r][k]);
+            v1 = fmaxf(v1, part[r][32 + k]);
+        }
+        rowb[(int64_t)blockIdx.x * Kp + i0 + r] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_pkrtz(v0, v1));
+    }
+}
 
 // Column maxima of log A as order keys (cmax zeroed before): each block takes
 // 64 columns of a share of the rows.  Also clears the teams' exchange buffers

@@ -251,6 +251,7 @@ struct EngineArgs {
     int32_t b_leaf;             // segments of at most this many positions keep backpointers
     int32_t b_split;            // longer ones are split into at most this many
     uint32_t* cmax;             // [K] column maxima of log A as order keys
+    uint32_t* rowb;             // bounded decodes: row bounds [Kp / 64, Kp], two float16: of either half of a group
     int32_t b_team;             // blocks of a team
     char* bscr;                 // per-team scratch: division copies or a leaf's backpointers
     int64_t bscr_bytes;

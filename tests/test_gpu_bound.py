@@ -62,3 +62,28 @@ def test_bounded_matches_oracle(K, kind):
                 assert np.float32(so).view(np.uint32) == scores[b].view(np.uint32), (b, so, scores[b])
                 assert (status[b] == fv.FV_OK) == bool(np.isfinite(so))
                 np.testing.assert_array_equal(paths[b][:T], po)
+
+
+@pytest.mark.parametrize("kind", ["normal", "ties", "missing", "sign", "positive", "flat"])
+@pytest.mark.parametrize("K", [320, 512, 513, 1000, 1024])
+def test_one_block_per_sequence(K, kind):
+    """Batches of more sequences than the card has blocks for teams."""
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    import paper_2510_19301_amd as fv
+    lens = [1, 2, 3] + [5, 6, 7] * 75
+    lp, la, lbs = _inputs(kind, K, lens)
+    dev = lambda x: torch.from_numpy(x).cuda()
+    d_la, d_lp = dev(la), dev(lp)
+    d_lbs = [dev(b) for b in lbs]
+    refs = [oracle.vanilla(lp, la, lb) for lb in lbs]
+    for method, P in (("vanilla", 1), ("flash", 2)):
+        print(f"{kind} K={K} {method} n={len(lens)}", flush=True)
+        batch = fv.Batch(d_lbs)
+        fv.decode_batch(d_la, batch, d_lp, method=method, P=P)
+        torch.cuda.synchronize()
+        paths, scores = batch.paths.cpu().numpy(), batch.scores.cpu().numpy()
+        for b, lb in enumerate(lbs):
+            po, so, _ = refs[b] if method == "vanilla" else oracle.flash(lp, la, lb, P)[:3]
+            assert np.float32(so).view(np.uint32) == scores[b].view(np.uint32), (b, so, scores[b])
+            np.testing.assert_array_equal(paths[b][:lb.shape[0]], po)
