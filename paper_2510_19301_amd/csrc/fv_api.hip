@@ -18,11 +18,11 @@ extern "C" __global__ void fv_engine_kernel(const EngineArgs* __restrict__ table
 extern "C" __global__ void fv_small_vanilla32_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_small_vanilla64_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_small_vanilla128_kernel(const EngineArgs* __restrict__ table);
-extern "C" __global__ void fv_small_vanilla256_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_small_flash32_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_small_flash64_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_small_flash128_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_small_flash256_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_bound256_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_bound512_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_bound1k_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_team1k_kernel(const EngineArgs* __restrict__ table);
@@ -179,8 +179,8 @@ size_t put(size_t& cur, Region& r, size_t bytes) {
 
 // Which of the bounded kernels decodes K states on teams of `team` blocks
 int team_kernel(int32_t K, int32_t team) {
-    if (team == 1) return K <= 512 ? 0 : 1;
-    return K <= 1024 ? 2 : (K <= 4096 ? 3 : 4);
+    if (team == 1) return K <= 256 ? 0 : (K <= 512 ? 1 : 2);
+    return K <= 1024 ? 3 : (K <= 4096 ? 4 : 5);
 }
 
 // Workspace layout of a dense decode.  Depends only on the arguments, so
@@ -315,6 +315,7 @@ fv_status plan_dense(int32_t method, const fv_trans* A, const int32_t* T_host, i
     put(cur, L.Ap, (!sparse && L.Kp != K) ? (size_t)L.Kp * L.Kp * 4 : 0);  // padded dense copy only when needed
     // transposed copy for the two-column items of moderate K
     put(cur, L.At, (!sparse && L.Kp <= kColMaxKp) ? (size_t)L.Kp * L.Kp * 4 : 0);
+    int32_t team_cap = 0;
     if (!sparse && !beam && K <= kBoundMaxK) {
         // a block owns up to kTeamGroups groups of 64 columns; teams get more
         // blocks (fewer groups each) while they can all work: as many teams
@@ -328,15 +329,16 @@ fv_status plan_dense(int32_t method, const fv_trans* A, const int32_t* T_host, i
         const int64_t work = (method == FV_FLASH ? 2 : 1) * L.sum_T;
         const int64_t busy = std::max<int64_t>(1, std::min(roots, (work + max_T - 1) / std::max<int64_t>(1, max_T)));
         L.team = (groups + kTeamGroups - 1) / kTeamGroups;
-        while (L.team * 2 <= groups && L.team * 2 * busy * 4 <= budget * 5) L.team *= 2;
-        L.teams = (int32_t)std::min<int64_t>(budget / L.team,
+        while (K > kBoundSmallK && L.team * 2 <= groups && L.team * 2 * busy * 4 <= budget * 5) L.team *= 2;
+        team_cap = L.team == 1 && K <= 256 ? 4 * budget : budget / L.team;
+        L.teams = (int32_t)std::min<int64_t>(team_cap,
                                              std::max(roots, method == FV_FLASH ? L.n_segs : (int64_t)0));
         L.xch_bytes = round_up(((L.team > 1 ? 2 * (int64_t)L.Kp + 2 * round_up(groups, 16) : 0) + 16 + L.team) * 8, kAlign);
     }
     put(cur, L.cmax, L.teams ? (size_t)K * 4 : 0);
-    put(cur, L.rowb, L.teams && team_kernel(K, L.team) == 1 ? (size_t)L.Kp * (L.Kp / 64) * 4 : 0);
+    put(cur, L.rowb, L.teams && team_kernel(K, L.team) == 2 ? (size_t)L.Kp * (L.Kp / 64) * 4 : 0);
     // (as many as can be resident, so that the size does not grow with P)
-    put(cur, L.xch, (size_t)(method == FV_FLASH && L.team ? kTeamBlocks / L.team : L.teams) * L.xch_bytes);
+    put(cur, L.xch, (size_t)(method == FV_FLASH ? team_cap : L.teams) * L.xch_bytes);
     put(cur, L.seq1, single ? sizeof(fv_seq) : 0);
     put(cur, L.seqinfo, (size_t)std::max(n_seqs, 1) * sizeof(SeqInfo));
     put(cur, L.keys, (size_t)std::max(n_seqs, 1) * 8);
@@ -408,7 +410,7 @@ void launch_transpose(const fv_trans* A, const DenseLayout& L, char* w, hipStrea
 struct DeviceInfo {
     int cus = 0;
     int engine_blocks_per_cu = 0;
-    int team_blocks_per_cu[5] = {0, 0, 0, 0, 0};   // one block K <= 512, 1024; teams K <= 1024, 4096, 16384
+    int team_blocks_per_cu[6] = {0, 0, 0, 0, 0, 0};   // one block K <= 256, 512, 1024; teams K <= 1024, 4096, 16384
 };
 
 // Queried once per device and cached: a decode call then does no property
@@ -451,13 +453,14 @@ fv_status device_info(DeviceInfo& di) {
         HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, reinterpret_cast<const void*>(fv_engine_kernel),
                                                              kEngineBlock, 0));
         d.engine_blocks_per_cu = nb;
-        const void* const team[5] = {reinterpret_cast<const void*>(fv_bound512_kernel),
+        const void* const team[6] = {reinterpret_cast<const void*>(fv_bound256_kernel),
+                                     reinterpret_cast<const void*>(fv_bound512_kernel),
                                      reinterpret_cast<const void*>(fv_bound1k_kernel),
                                      reinterpret_cast<const void*>(fv_team1k_kernel),
                                      reinterpret_cast<const void*>(fv_team4k_kernel),
                                      reinterpret_cast<const void*>(fv_team16k_kernel)};
-        for (int k = 0; k < 5; ++k)
-            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&d.team_blocks_per_cu[k], team[k], kTeamBlock, 0));
+        for (int k = 0; k < 6; ++k)
+            HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&d.team_blocks_per_cu[k], team[k], k == 0 ? kBlock : kTeamBlock, 0));
         if (nb < 1) return fail(FV_E_DEVICE, "engine kernel cannot be resident");
         g_dev_info[dev] = d;
         g_dev_known[dev] = true;
@@ -489,7 +492,11 @@ BoundPlan plan_bounded(uint32_t flags, int32_t method, const fv_trans* A, const 
     BoundPlan b;
     // flags that ask for a placement, a kernel or the full bisection, and
     // the engine's own hooks, mean the lock-step engine
-    if (!L.teams || (flags & ~(uint32_t)FV_FLAG_VALIDATE) || g_dbg_max_steps || g_dbg_spin_limit || g_dbg_trace) return b;
+    // (which small models' block per sequence has no part in)
+    if (!L.teams || (flags & FV_FLAG_ENGINE)) return b;
+    if (A->K > kBoundSmallK && ((flags & ~(uint32_t)FV_FLAG_VALIDATE) || g_dbg_max_steps ||
+                                g_dbg_spin_limit || g_dbg_trace))
+        return b;
     // the blocks of the teams wait for each other: all of them are resident
     const int32_t resident = di.cus * di.team_blocks_per_cu[team_kernel(A->K, L.team)];
     if (resident < L.team) return b;
@@ -661,13 +668,20 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
     std::vector<EngineArgs> args(bp.L.size());
     std::vector<const float*> aps(bp.L.size());
     std::vector<BoundPlan> bounds(bp.L.size());
-    // vanilla or FLASH decodes whose models are all small and dense: one block per sequence, one
-    // launch per model
+    // vanilla or FLASH decodes whose models are all small and dense: one block
+    // per sequence, one launch per model.  Every candidate is scanned, from
+    // registers, which up to K = 128 takes less than a bounded scan's steps
+    // (K = 100, T = 1000, vanilla: 1.9 against 2.5 ms; 256 sequences of K = 128:
+    // 2.0 against 2.6), beyond it more (K = 130, T = 1000, vanilla: 6.0 against
+    // 2.5 ms; 512 sequences of K = 256, FLASH with gradients: 12.7 against 2.6).
+    // Bisections to the paper's minimum stay here up to K = 256: bounded FLASH
+    // passes end in leaves.
+    const int32_t small_k = flags & (FV_FLAG_RELATIVE_INIT | FV_FLAG_NO_LEAVES) ? kSmallFlashK : kSmallK;
     bool small = !(flags & FV_FLAG_ENGINE);
     for (size_t p = 0; p < bp.L.size(); ++p) {
         const int32_t K_ = bp.L[p].K;
         small = small && models[bp.model[p]].kind == FV_DENSE &&
-                ((bp.method[p] == FV_VANILLA && K_ <= kSmallK) || (bp.method[p] == FV_FLASH && K_ <= kSmallFlashK));
+                ((bp.method[p] == FV_VANILLA && K_ <= kSmallK) || (bp.method[p] == FV_FLASH && K_ <= small_k));
     }
     bool engine = false;   // the lock-step engine is launched
     for (size_t p = 0; p < bp.L.size() && !small; ++p) {
@@ -860,9 +874,7 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
             const dim3 block(Ks <= 64 ? 64 : (Ks <= 128 ? 128 : 256));
             if (bp.method[p] == FV_VANILLA)
                 hipLaunchKernelGGL(Ks <= 32 ? fv_small_vanilla32_kernel
-                                            : (Ks <= 64 ? fv_small_vanilla64_kernel
-                                                        : (Ks <= 128 ? fv_small_vanilla128_kernel
-                                                                     : fv_small_vanilla256_kernel)),
+                                            : (Ks <= 64 ? fv_small_vanilla64_kernel : fv_small_vanilla128_kernel),
                                    grid, block, 0, stream, table_dev + p);
             else
                 hipLaunchKernelGGL(Ks <= 32 ? fv_small_flash32_kernel
@@ -878,14 +890,15 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         const EngineArgs* ta = table_dev + p;
         void* targs[] = {&ta};
         const dim3 grid(bounds[p].teams * bp.L[p].team);
-        const void* const team[5] = {reinterpret_cast<const void*>(fv_bound512_kernel),
+        const void* const team[6] = {reinterpret_cast<const void*>(fv_bound256_kernel),
+                                     reinterpret_cast<const void*>(fv_bound512_kernel),
                                      reinterpret_cast<const void*>(fv_bound1k_kernel),
                                      reinterpret_cast<const void*>(fv_team1k_kernel),
                                      reinterpret_cast<const void*>(fv_team4k_kernel),
                                      reinterpret_cast<const void*>(fv_team16k_kernel)};
         const void* const fn = team[team_kernel(K, bp.L[p].team)];
         if (bp.L[p].team > 1) HIP_TRY(hipLaunchCooperativeKernel(fn, grid, dim3(kTeamBlock), targs, 0, stream));
-        else HIP_TRY(hipLaunchKernel(fn, grid, dim3(kTeamBlock), targs, 0, stream));
+        else HIP_TRY(hipLaunchKernel(fn, grid, dim3(K <= 256 ? kBlock : kTeamBlock), targs, 0, stream));
         if (bounds[p].rows > 0 && args[p].At)
             hipLaunchKernelGGL(fv_transpose_dense_kernel, dim3(args[p].Kp / 64, args[p].Kp / 64), dim3(kBlock), 0,
                                stream, args[p].Acol, args[p].Kp, const_cast<float*>(args[p].At), &args[p].st->q_tail0);

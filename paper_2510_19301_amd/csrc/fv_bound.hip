@@ -62,10 +62,7 @@ constexpr int kTiers = 3;
 // second reading in 78% instead of 35% of the steps and takes 20% longer)
 constexpr float kNear = 0.9f, kFar = 1.4f, kHalf = 1.15f, kEma = 0.2f;
 constexpr int32_t kBoundRetry = 77;   // sequence status: left to the lock-step engine
-constexpr int kTCols = 64 * kTeamGroups;   // columns of a block, at most
 constexpr int kRowCap = 128;          // rows of a wave's lists (FILTER)
-constexpr int kUnit = 8;              // list entries of a unit of work
-constexpr int kUnitLoads = kUnit / 4; // 16 lanes across 64 columns: 4 entries side by side
 
 // A candidate and its predecessor as one float64 pattern: the float32 score
 // in the high word, the state in the low word.  Finite scores and infinities
@@ -87,18 +84,19 @@ struct BoundEnt {
 // wait comes once every NB steps.)
 template <int KC, int LC, int NB, bool TEAM, bool FILTER>
 struct TeamLds {
+    static constexpr int TC = KC < 64 * kTeamGroups ? KC : 64 * kTeamGroups;   // columns of a block, at most
     union {
         struct {
             BoundEnt list[FILTER ? 1 : kTiers][LC];   // scanned states, unordered
             BoundEnt rows[FILTER ? 16 : 1][2][FILTER ? kRowCap + 16 : 1];   // a wave's rows to read, by half of its group
-            float eb[2][NB * kTCols];       // emission rows of the block's columns: in use, and coming
+            float eb[2][NB * TC];       // emission rows of the block's columns: in use, and coming
         };
-        uint32_t walk[(8 * (FILTER ? 1 : kTiers) * LC + (FILTER ? 256 * (kRowCap + 16) : 16) + 8 * NB * kTCols) / 4];   // backpointer rows being walked
+        uint32_t walk[(8 * (FILTER ? 1 : kTiers) * LC + (FILTER ? 256 * (kRowCap + 16) : 16) + 8 * NB * TC) / 4];   // backpointer rows being walked
     };
-    unsigned long long part[FILTER ? 1 : kTCols];   // order keys of partial maxima
+    unsigned long long part[FILTER ? 1 : TC];   // order keys of partial maxima
     uint32_t rb[FILTER ? 16 * KC : 1];   // [groups, Kp] row bounds of both halves
-    float cm[kTCols];                  // column maxima; NaN where no scan is ever needed
-    uint16_t pb[2][NB * kTCols];       // backpointer rows: being made, being stored
+    float cm[TC];                  // column maxima; NaN where no scan is ever needed
+    uint16_t pb[2][NB * TC];       // backpointer rows: being made, being stored
     uint16_t anc[TEAM ? 1 : 2][KC];    // tracked division state of every state
     float x[TEAM ? 1 : 2][TEAM ? 1 : KC];   // a single block's scores, by step parity
     uint32_t rmax[2];                  // and the order key of the largest
@@ -239,7 +237,10 @@ enum : int32_t { BM_VANILLA = 0, BM_DIV = 1, BM_LEAF = 2 };
 template <int KC, int LC, int NB, bool TEAM, int W, bool FILTER>
 __device__ __forceinline__ void team_decode(cargs_t& a) {
     constexpr int kTThreads = 64 * W;
+    constexpr int TC = TeamLds<KC, LC, NB, TEAM, FILTER>::TC;
     constexpr int GPW = 1;   // groups of a wave, at most
+    constexpr int UN = KC <= 256 ? 16 : 8;   // list entries of a unit of work
+    constexpr int UL = UN / 4;               // 16 lanes across 64 columns: 4 entries side by side
     // long rows: the groups' maxima are polled first, the words then read once
     constexpr bool GATE = TEAM && KC > 4096;
     __shared__ __align__(16) TeamLds<KC, LC, NB, TEAM, FILTER> s;
@@ -275,7 +276,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
         if (!FILTER) jl = g * 64 + lc4 + (lane >> 4);
         active = g < ngl;
     };
-    for (int32_t k = tid; k < kTCols; k += kTThreads) {
+    for (int32_t k = tid; k < TC; k += kTThreads) {
         const float c = k < cn ? score_of_key(a.cmax[cb + k]) : -INFINITY;
         s.cm[k] = c > -INFINITY ? c : __builtin_nanf("");
     }
@@ -390,21 +391,21 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
         auto link = [&]() { return reinterpret_cast<int32_t*>(dsnap() + (int64_t)(w - 1) * Kp); };
         // backpointer rows: the sequence's table (row t), or the leaf's (row t - m - 1)
         const int32_t tab0 = mode == BM_VANILLA ? 0 : m + 1;
+        uint16_t* const psi = a.psi16 + sq.psi_off;
         auto table = [&]() {
-            return mode == BM_VANILLA ? a.psi16 + seq_info().psi_off : reinterpret_cast<uint16_t*>(scratch());
+            return mode == BM_VANILLA ? psi : reinterpret_cast<uint16_t*>(scratch());
         };
         auto div_end = [&](int32_t k) { return m + (int32_t)((((int64_t)k + 1) * len - 1) / w); };
+        const float* const lb = sq.log_b + cb;
+        const int64_t ld = sq.ld;
         // emission rows t0 .. t0 + NB - 1 into LDS (no registers held); 64 columns a wave and instruction
         auto fetch = [&](int32_t half, int32_t t0) {
             typedef __attribute__((address_space(3))) void lvoid_t;
             typedef __attribute__((address_space(1))) const void gvoid_t;
-            const SeqInfo& si = seq_info();
-            const float* const lb = si.log_b + cb;
-            const int64_t ld = si.ld;
             for (int32_t q = wv; q < ngl * NB; q += W) {
                 const int32_t r = q % NB, c = q / NB;
                 lvoid_t* dst = reinterpret_cast<lvoid_t*>((uint32_t)__builtin_amdgcn_readfirstlane(
-                    (int32_t)(uintptr_t)&s.eb[half][r * kTCols + c * 64]));
+                    (int32_t)(uintptr_t)&s.eb[half][r * TC + c * 64]));
                 if (t0 + r <= n && c * 64 + lane < cn)
                     __builtin_amdgcn_global_load_lds(
                         reinterpret_cast<gvoid_t*>(
@@ -417,15 +418,15 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             const uint16_t* const rows = s.pb[half];
             uint16_t* const dst = table() + (int64_t)(t0 - tab0) * K + cb;
             if (K & 1) {
-                for (int32_t k = tid; k < cnt * kTCols; k += kTThreads) {
-                    const int32_t c = k % kTCols;
-                    if (c < cn) st_c(dst + (int64_t)(k / kTCols) * K + c, rows[k]);
+                for (int32_t k = tid; k < cnt * TC; k += kTThreads) {
+                    const int32_t c = k % TC;
+                    if (c < cn) st_c(dst + (int64_t)(k / TC) * K + c, rows[k]);
                 }
             } else {
-                for (int32_t k = tid; k < cnt * (kTCols / 2); k += kTThreads) {
-                    const int32_t c = 2 * (k % (kTCols / 2));
+                for (int32_t k = tid; k < cnt * (TC / 2); k += kTThreads) {
+                    const int32_t c = 2 * (k % (TC / 2));
                     if (c < cn)
-                        st_c(reinterpret_cast<uint32_t*>(dst + (int64_t)(k / (kTCols / 2)) * K + c),
+                        st_c(reinterpret_cast<uint32_t*>(dst + (int64_t)(k / (TC / 2)) * K + c),
                              reinterpret_cast<const uint32_t*>(rows)[k]);
                 }
             }
@@ -545,9 +546,9 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             float h0, h1, h2;
             for (int32_t go = 0;; ++go) {
             const float gx = (step == 0 ? G1 : G) * __int_as_float((127 - go) << 23);
-            h0 = D - (FILTER ? kNear : (wpg > 1 ? 1.0f : 0.75f)) * gx;
-            h1 = D - (FILTER ? kFar : (wpg > 1 ? 1.2f : 1.0f)) * gx;
-            h2 = FILTER ? h1 : D - (GATE ? 1.4f : (wpg > 1 ? 1.7f : 1.35f)) * gx;
+            h0 = D - (FILTER ? kNear : (wpg > 1 || KC <= 256 ? 1.0f : 0.75f)) * gx;
+            h1 = D - (FILTER ? kFar : (wpg > 1 || KC <= 256 ? 1.2f : 1.0f)) * gx;
+            h2 = FILTER ? h1 : D - (GATE ? 1.4f : (wpg > 1 || KC <= 256 ? 1.7f : 1.35f)) * gx;
 #pragma unroll
             for (int c = 0; c < NS; c += CN) {
                 if (c * kTThreads >= K) break;
@@ -602,7 +603,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             __syncthreads();
             }
             if (wpg > 1)
-                for (int32_t k = tid; k < kTCols; k += kTThreads) s.part[k] = 0;
+                for (int32_t k = tid; k < TC; k += kTThreads) s.part[k] = 0;
             if (tid == 0) s.need[par ^ 1] = 0;   // every wave is past its reads of the step before
             if (tid == 1) s.rmax[xp ^ 1] = 0;
             const bool quit = TEAM && LC < KC && s.sv[7] != 0;
@@ -730,7 +731,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 }
                 const float b = __int_as_float(__double2hiint(top));
                 const int32_t arg = b > -INFINITY ? __double2loint(top) ^ flip : 0;
-                const float xn = jl < cn ? b + s.eb[half][row * kTCols + jl] : -INFINITY;
+                const float xn = jl < cn ? b + s.eb[half][row * TC + jl] : -INFINITY;
                 int32_t mid = 0;
                 if (mode == BM_DIV) {
                     mid = e_prev == t - 1 ? arg : (t > e_first + 1 ? s.anc[TEAM ? 0 : xp][arg] : 0);
@@ -739,7 +740,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                         if (d_next >= 1) st_c(link() + (int64_t)d_next * Kp + cb + jl, mid);
                     }
                 } else {
-                    s.pb[half][row * kTCols + jl] = (uint16_t)arg;
+                    s.pb[half][row * TC + jl] = (uint16_t)arg;
                 }
                 publish(t, xn, mid);
                 // what the next step's lists are made from, off the path of its scores
@@ -897,10 +898,10 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             if (active) {
                 for (; k < min(wpg > 1 ? 2 : 1, lists); ++k) {
                     const BoundEnt* const list = s.list[k];
-                    const int32_t cnt = uni(s.cnt[par][k]), inc = wpg * kUnit;
-                    BoundEnt e0[kUnitLoads], e1[kUnitLoads];
-                    vec_t v0[kUnitLoads], v1[kUnitLoads];
-                    int32_t e = sub * kUnit;
+                    const int32_t cnt = uni(s.cnt[par][k]), inc = wpg * UN;
+                    BoundEnt e0[UL], e1[UL];
+                    vec_t v0[UL], v1[UL];
+                    int32_t e = sub * UN;
                     if (e >= cnt) continue;
                     load(e0, v0, list, e, cnt, add);
                     for (; e + 2 * inc < cnt; e += 2 * inc) {
@@ -934,9 +935,9 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 while (!stop && k < lists) {
                     const int32_t cnt = uni(s.cnt[par][k]);
                     double more[4] = {none, none, none, none};
-                    for (int32_t e = 0; e < cnt; e += 2 * kUnit) {
-                        BoundEnt e0[2 * kUnitLoads];
-                        vec_t v0[2 * kUnitLoads];
+                    for (int32_t e = 0; e < cnt; e += 2 * UN) {
+                        BoundEnt e0[2 * UL];
+                        vec_t v0[2 * UL];
                         load(e0, v0, s.list[k], e, cnt, add);
                         scan(more, e0, v0);
                     }
@@ -1179,19 +1180,23 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
     if (lane == 0) st->q_tail0 = left;
 }
 
-// One block per task for K <= 512 and 1024, teams for K <= 1024, 4096 and
-// 16384; a block takes a CU's 16 wavefronts (two blocks of 8 for one task
+// One block per task for K <= 256, 512 and 1024, teams for K <= 1024, 4096
+// and 16384.  A block takes a CU's 16 wavefronts (two blocks of 8 for one task
 // each: 158 instead of 112 ms for 256 sequences of K = 1024, FLASH P = 64, whose
-// roots then leave half of them idle).
-#define FV_TEAM(NAME, KC, LC, NB, TEAM, FILTER)                                                                 \
-    extern "C" __global__ __launch_bounds__(1024, 4) void NAME(const EngineArgs* __restrict__ table) {           \
-        team_decode<KC, LC, NB, TEAM, 16, FILTER>(*reinterpret_cast<cargs_t*>(reinterpret_cast<uint64_t>(table))); \
+// roots then leave half of them idle); up to K = 256, with a wave for each
+// group and rows enough for one or two units, three blocks of 4 share a CU:
+// 512 sequences of K = 256, T ~ U[32, 512], FLASH P = 16 and the score's gradients
+// take 2.6 ms (8 waves each: 2.5, 16: 3.9; 64 sequences of K = 200: 1.5, 1.7, 1.7).
+#define FV_TEAM(NAME, KC, LC, NB, TEAM, W, FILTER)                                                              \
+    extern "C" __global__ __launch_bounds__(64 * W, W == 4 ? 3 : 4) void NAME(const EngineArgs* __restrict__ table) {           \
+        team_decode<KC, LC, NB, TEAM, W, FILTER>(*reinterpret_cast<cargs_t*>(reinterpret_cast<uint64_t>(table))); \
     }
-FV_TEAM(fv_bound512_kernel, 1024, 1024, 4, false, false)
-FV_TEAM(fv_bound1k_kernel, 1024, 1024, 2, false, true)
-FV_TEAM(fv_team1k_kernel, 1024, 1024, 4, true, false)
-FV_TEAM(fv_team4k_kernel, 4096, 2048, 4, true, false)
-FV_TEAM(fv_team16k_kernel, 16384, 2048, 2, true, false)
+FV_TEAM(fv_bound256_kernel, 256, 256, 8, false, 4, false)
+FV_TEAM(fv_bound512_kernel, 1024, 1024, 4, false, 16, false)
+FV_TEAM(fv_bound1k_kernel, 1024, 1024, 2, false, 16, true)
+FV_TEAM(fv_team1k_kernel, 1024, 1024, 4, true, 16, false)
+FV_TEAM(fv_team4k_kernel, 4096, 2048, 4, true, 16, false)
+FV_TEAM(fv_team16k_kernel, 16384, 2048, 2, true, 16, false)
 #undef FV_TEAM
 
 // Row bounds: rowb[g][i] (two float16) >= max over the 32 columns of either half

@@ -3715,7 +3715,7 @@ FV_SMALL_VANILLA(fv_small_vanilla32_kernel, 32)
 FV_SMALL_VANILLA(fv_small_vanilla64_kernel, 64)
 #undef FV_SMALL_VANILLA
 
-// 64 < K <= 256: KMAX / 64 waves per sequence (KMAX = 128 or 256), thread j
+// 64 < K <= 128: KMAX / 64 waves per sequence, thread j
 // for destination j (its column of log A in registers; one wave with
 // several columns per lane would need more than the whole register file).  Each step publishes the
 // scores in LDS, double-buffered so that one barrier per step suffices, and
@@ -3802,10 +3802,6 @@ __device__ __forceinline__ void small_vanilla_waves(const EngineArgs* __restrict
 
 extern "C" __global__ __launch_bounds__(128) void fv_small_vanilla128_kernel(const EngineArgs* __restrict__ table) {
     small_vanilla_waves<128>(table);
-}
-
-extern "C" __global__ __launch_bounds__(256) void fv_small_vanilla256_kernel(const EngineArgs* __restrict__ table) {
-    small_vanilla_waves<256>(table);
 }
 
 // ---------------------------------------------------------------- small single FLASH decode

@@ -82,11 +82,13 @@ constexpr int kTeamGroups = 16;
 constexpr int32_t kTeamBlocks = 256;
 constexpr int64_t kTeamSpin = (int64_t)1 << 28;
 
-// One vanilla decode of a dense model with K <= kSmallK runs on one wave
-// instead of the persistent engine.
-constexpr int32_t kSmallK = 256;
-// One FLASH decode of a dense model with K <= kSmallFlashK runs on one wave too.
+// Vanilla and FLASH decodes of a dense model with K <= kSmallK, and FLASH
+// bisections to the paper's minimum with K <= kSmallFlashK, run on one block
+// per sequence that scans every candidate; other dense decodes are bounded
+// scans, up to K = kBoundSmallK on one small block per sequence.
+constexpr int32_t kSmallK = 128;
 constexpr int32_t kSmallFlashK = 256;
+constexpr int32_t kBoundSmallK = 256;
 
 // Operations of a beam row (one block each): start step, full beam step,
 // end-only step of a subtask, final selection of a root.

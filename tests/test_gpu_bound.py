@@ -12,9 +12,9 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 LENS = [1, 2, 3, 6, 21, 70]
-# state counts: one group past the small models, odd rows, a partial last
-# group, the single block's largest, the teams' kernels on both sides
-KS = [257, 300, 512, 577, 1000, 1023, 1024, 1025, 2047, 4096, 4097]
+# state counts: past the small models, odd rows, a partial last group, the
+# single blocks' largest, the teams' kernels on both sides
+KS = [129, 130, 192, 255, 256, 257, 300, 512, 577, 1000, 1023, 1024, 1025, 2047, 4096, 4097]
 
 
 def _inputs(kind, K, lens):
@@ -65,7 +65,7 @@ def test_bounded_matches_oracle(K, kind):
 
 
 @pytest.mark.parametrize("kind", ["normal", "ties", "missing", "sign", "positive", "flat"])
-@pytest.mark.parametrize("K", [320, 512, 513, 1000, 1024])
+@pytest.mark.parametrize("K", [131, 256, 320, 512, 513, 1000, 1024])
 def test_one_block_per_sequence(K, kind):
     """Batches of more sequences than the card has blocks for teams."""
     if not torch.cuda.is_available():
