@@ -28,6 +28,8 @@ extern "C" __global__ void fv_bound1k_kernel(const EngineArgs* __restrict__ tabl
 extern "C" __global__ void fv_team1k_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_team4k_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_team16k_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_beam_dense_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_beam_sparse_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_colmax_kernel(const float* __restrict__ log_a, int32_t K, uint32_t* __restrict__ cmax,
                                             uint4* __restrict__ zero, int64_t nzero);
 extern "C" __global__ void fv_rowbound_kernel(const float* __restrict__ Ap, int32_t K, int32_t Kp,
@@ -410,6 +412,7 @@ void launch_transpose(const fv_trans* A, const DenseLayout& L, char* w, hipStrea
 struct DeviceInfo {
     int cus = 0;
     int engine_blocks_per_cu = 0;
+    int beam_blocks_per_cu[2] = {0, 0};   // dense, sparse
     int team_blocks_per_cu[6] = {0, 0, 0, 0, 0, 0};   // one block K <= 256, 512, 1024; teams K <= 1024, 4096, 16384
 };
 
@@ -461,6 +464,10 @@ fv_status device_info(DeviceInfo& di) {
                                      reinterpret_cast<const void*>(fv_team16k_kernel)};
         for (int k = 0; k < 6; ++k)
             HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&d.team_blocks_per_cu[k], team[k], k == 0 ? kBlock : kTeamBlock, 0));
+        HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &d.beam_blocks_per_cu[0], reinterpret_cast<const void*>(fv_beam_dense_kernel), kTeamBlock, 0));
+        HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &d.beam_blocks_per_cu[1], reinterpret_cast<const void*>(fv_beam_sparse_kernel), kTeamBlock, 0));
         if (nb < 1) return fail(FV_E_DEVICE, "engine kernel cannot be resident");
         g_dev_info[dev] = d;
         g_dev_known[dev] = true;
@@ -684,7 +691,12 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
                 ((bp.method[p] == FV_VANILLA && K_ <= kSmallK) || (bp.method[p] == FV_FLASH && K_ <= small_k));
     }
     bool engine = false;   // the lock-step engine is launched
+    std::vector<int32_t> beams(bp.L.size(), 0);   // blocks of a beam decode off the engine
     for (size_t p = 0; p < bp.L.size() && !small; ++p) {
+        const fv_trans* A = &models[bp.model[p]];
+        if (bp.method[p] == FV_BEAM && !(flags & ~(uint32_t)FV_FLAG_VALIDATE) && !g_dbg_max_steps && !g_dbg_spin_limit &&
+            !g_dbg_trace && std::min(B, A->K) <= kBeamBlockB && (A->kind == FV_CSR || A->K <= kBeamBlockK))
+            beams[p] = di.cus * std::max(1, di.beam_blocks_per_cu[A->kind == FV_CSR ? 1 : 0]);
         bounds[p] = plan_bounded(flags, bp.method[p], &models[bp.model[p]], bp.L[p], di);
         engine = engine || bounds[p].teams == 0 || bounds[p].rows > 0;
     }
@@ -813,8 +825,8 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         a.spin_limit = g_dbg_spin_limit ? g_dbg_spin_limit : (int64_t)1 << 24;
         // beam: exact re-decodes add at most one pass per subtask
         a.max_steps = g_dbg_max_steps ? g_dbg_max_steps : (meth == FV_BEAM ? 16 : 8) * (L.sum_T + L.n_tasks) + 4096;
+        a.bounded = bnd.teams || beams[p];
         if (bnd.teams) {
-            a.bounded = 1;
             a.b_leaf = bnd.leaf;
             a.b_split = bnd.split;
             a.b_team = L.team;
@@ -884,6 +896,10 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
                                    grid, block, 0, stream, table_dev + p);
         }
     }
+    for (size_t p = 0; p < bp.L.size(); ++p)
+        if (beams[p])
+            hipLaunchKernelGGL(models[bp.model[p]].kind == FV_CSR ? fv_beam_sparse_kernel : fv_beam_dense_kernel,
+                               dim3(beams[p]), dim3(kTeamBlock), 0, stream, table_dev + p);
     for (size_t p = 0; p < bp.L.size(); ++p) {
         if (!bounds[p].teams) continue;
         const int32_t K = bp.L[p].K;

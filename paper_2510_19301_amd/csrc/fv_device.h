@@ -126,4 +126,40 @@ __device__ __forceinline__ float emission(cargs_t& a, const float* lb, int64_t l
     return emission_of(a.emit_kind, a.emit_xy, a.emit_c2, a.emit_c0, lb, ld, t, j);
 }
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t v) {   // zero where no lane is the source
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, CTRL, ROWS, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {   // in every lane
+    v = max(v, dpp_u<0x111, 0xf>(v));   // row_shr:1
+    v = max(v, dpp_u<0x112, 0xf>(v));
+    v = max(v, dpp_u<0x114, 0xf>(v));
+    v = max(v, dpp_u<0x118, 0xf>(v));
+    v = max(v, dpp_u<0x142, 0xa>(v));   // row_bcast:15
+    v = max(v, dpp_u<0x143, 0xc>(v));   // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int32_t)v, 63);
+}
+// fmax would first quiet its operands, a second instruction for each
+__device__ __forceinline__ double max64(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double swap_max32(double a, double b) {   // low lanes: max of a's halves, high lanes: of b's
+    const auto l = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return max64(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+}
+__device__ __forceinline__ double swap_max16(double a, double b) {   // even rows: max of a's row pair, odd rows: of b's
+    const auto l = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return max64(__hiloint2double(h[0], l[0]), __hiloint2double(h[1], l[1]));
+}
+// Merges the partial maxima of the lanes that scanned the same four columns
+// (lanes equal modulo 16) and spreads the columns over them: row r of 16 lanes
+// ends with column 4 (lane mod 16) + r.
+__device__ __forceinline__ double merge_group(const double (&b)[4]) {
+    return swap_max16(swap_max32(b[0], b[2]), swap_max32(b[1], b[3]));
+}
+
 }  // namespace fv

@@ -4487,7 +4487,7 @@ extern "C" __global__ __launch_bounds__(kBlock) void fv_setup_kernel(EngineArgs 
     for (int32_t k = tid; k < (int32_t)(sizeof(EngineState) / 4); k += kBlock) words[k] = 0;
     for (int32_t k = tid; k < a.n_compute_blocks + 1; k += kBlock) a.arrive[k] = 0;
     __syncthreads();
-    if (a.bounded)
+    if (a.cmax)
         for (int32_t k = tid; k < a.K; k += kBlock) a.cmax[k] = 0;
     if (tid == 0) {
         st->q_tail0 = n_tasks;

@@ -89,6 +89,10 @@ constexpr int64_t kTeamSpin = (int64_t)1 << 28;
 constexpr int32_t kSmallK = 128;
 constexpr int32_t kSmallFlashK = 256;
 constexpr int32_t kBoundSmallK = 256;
+// Beam decodes on one block per task (fv_beam.hip): widest beam, and states of
+// a dense model.
+constexpr int32_t kBeamBlockB = 256;
+constexpr int32_t kBeamBlockK = 2048;
 
 // Operations of a beam row (one block each): start step, full beam step,
 // end-only step of a subtask, final selection of a root.
@@ -248,7 +252,7 @@ struct EngineArgs {
     int32_t emit_kind;
     const double* emit_xy;      // [K][2] state points
     double emit_c2, emit_c0;    // log B_t(j) = (float)(c2 * d2 - c0)
-    // bounded decode (dense models, fv_bound.hip)
+    // decodes off the lock-step engine (fv_bound.hip, fv_beam.hip)
     int32_t bounded;            // the decode started there: the engine takes what is left in the queue
     int32_t b_leaf;             // segments of at most this many positions keep backpointers
     int32_t b_split;            // longer ones are split into at most this many
