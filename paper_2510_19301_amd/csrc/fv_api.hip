@@ -719,10 +719,10 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         // copies of log A: padded, and for the engine transposed (wide rows never
         // use that; after a bounded decode only if it left anything)
         const bool wide = use_wide_rows(flags, A->K, n_local, sparse);
-        const bool pad = !sparse && L.Kp != A->K;
+        const bool pad = !sparse && L.Kp != A->K && !small;   // (small models' kernels read log A once)
         if (pad) Ap = static_cast<const float*>(at(L.Ap));
         aps[p] = Ap;
-        float* const At = L.At.bytes && !wide ? static_cast<float*>(at(L.At)) : nullptr;
+        float* const At = L.At.bytes && !wide && !small ? static_cast<float*>(at(L.At)) : nullptr;
         if (pad) {
             const int64_t cells = (int64_t)L.Kp * L.Kp;
             hipLaunchKernelGGL(fv_prep_dense_kernel, dim3((unsigned)((cells + kBlock - 1) / kBlock)), dim3(kBlock),
@@ -762,6 +762,7 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         a.Kp = L.Kp;
         a.log_pi = log_pi ? log_pi[bp.model[p]] : nullptr;
         a.Acol = Ap;
+        a.a_pitch = small ? A->K : L.Kp;
         a.At = At;
         a.seqs = static_cast<SeqInfo*>(at(L.seqinfo));
         a.n_seqs = n_local;

@@ -3579,9 +3579,45 @@ constexpr int32_t kSmallPrefetch = 4;
 // chains (first maximum each), merged so that the larger value wins and
 // equal values (-0 == +0) go to the lower index: the same result as one
 // scan in index order.
+//
+// Where every score is negative (log probabilities), a candidate and its
+// predecessor make one float64 pattern, score in the high word and state in
+// the low word, and one v_max_f64 keeps the maximum and, of equal negative
+// scores, the lowest state: three instructions a candidate (read, add, max)
+// instead of five.  The low words stay in registers (lo[i] = i, hidden from
+// the compiler, which would otherwise make each anew every step).  A step with a
+// result that is not negative is taken again by value.
 template <int KMAX, int NJ>
-__device__ __forceinline__ void small_candidates(const float (&col)[NJ][KMAX], const float (&d)[NJ],
-                                                 float (&best)[NJ], int32_t (&arg)[NJ]) {
+__device__ __forceinline__ void small_candidates(const float (&col)[NJ][KMAX], const int32_t (&lo)[KMAX],
+                                                 const float (&d)[NJ], float (&best)[NJ], int32_t (&arg)[NJ]) {
+    bool up = false;
+#pragma unroll
+    for (int c = 0; c < NJ; ++c) up = up || d[c] >= 0.0f;
+    if (__builtin_amdgcn_ballot_w64(up) == 0) {
+        const double none = __hiloint2double((int32_t)0xff800000u, 0);
+        double b0[NJ], b1[NJ];
+#pragma unroll
+        for (int c = 0; c < NJ; ++c) b0[c] = b1[c] = none;
+#pragma unroll
+        for (int i = 0; i < KMAX; i += 2) {
+            const float d0 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d[i / 64]), i % 64));
+            const float d1 = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(d[(i + 1) / 64]), (i + 1) % 64));
+#pragma unroll
+            for (int c = 0; c < NJ; ++c) {
+                b0[c] = max64(b0[c], __hiloint2double(__float_as_int(d0 + col[c][i]), lo[i]));
+                b1[c] = max64(b1[c], __hiloint2double(__float_as_int(d1 + col[c][i + 1]), lo[i + 1]));
+            }
+        }
+        bool again = false;
+#pragma unroll
+        for (int c = 0; c < NJ; ++c) {
+            const double m = max64(b0[c], b1[c]);
+            best[c] = __int_as_float(__double2hiint(m));
+            arg[c] = best[c] > -INFINITY ? __double2loint(m) : 0;
+            again = again || best[c] >= 0.0f;
+        }
+        if (__builtin_amdgcn_ballot_w64(again) == 0) return;
+    }
     float b1[NJ];
     int32_t a1[NJ];
 #pragma unroll
@@ -3611,6 +3647,52 @@ __device__ __forceinline__ void small_candidates(const float (&col)[NJ][KMAX], c
         }
     }
 }
+template <int KMAX>
+__device__ __forceinline__ void small_states(int32_t (&lo)[KMAX]) {
+#pragma unroll
+    for (int i = 0; i < KMAX; ++i) asm volatile("v_mov_b32 %0, %1" : "=v"(lo[i]) : "n"(i));
+}
+
+// Backtrace of rows 1 .. T - 1 of a table that this block wrote, from state q
+// at T - 1: rows come to LDS in coalesced chunks (a walk in memory waits for
+// each entry, 0.3 us a step).  Every thread of the block calls it.
+constexpr int32_t kSmallWalk = 4096;   // entries in LDS
+__device__ __forceinline__ void small_walk(const uint16_t* psi, int32_t K, int32_t T, int32_t q, int32_t* path,
+                                           uint16_t* buf) {
+    const int32_t tid = threadIdx.x, per = kSmallWalk / K;
+    for (int32_t hi = T - 1; hi > 0; hi -= per) {
+        const int32_t lo = max(1, hi - per + 1), n = (hi - lo + 1) * K;
+        const uint16_t* src = psi + (int64_t)lo * K;
+        __syncthreads();
+        if (reinterpret_cast<uintptr_t>(src) % 16 == 0 && n % 8 == 0) {
+            const uint4* s4 = reinterpret_cast<const uint4*>(src);
+            for (int32_t k = tid; k < n / 8; k += 4 * blockDim.x) {
+                uint4 v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = s4[min(k + u * (int32_t)blockDim.x, n / 8 - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (k + u * (int32_t)blockDim.x < n / 8)
+                        reinterpret_cast<uint4*>(buf)[k + u * (int32_t)blockDim.x] = v[u];
+            }
+        } else {
+            for (int32_t k = tid; k < n; k += 8 * blockDim.x) {
+                uint16_t v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = src[min(k + u * (int32_t)blockDim.x, n - 1)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (k + u * (int32_t)blockDim.x < n) buf[k + u * (int32_t)blockDim.x] = v[u];
+            }
+        }
+        __syncthreads();
+        if (tid == 0)
+            for (int32_t t = hi; t >= lo; --t) {
+                q = clampi(buf[(t - lo) * K + q], K);
+                path[t - 1] = q;
+            }
+    }
+}
 
 template <int KMAX>
 __device__ __forceinline__ void small_vanilla(cargs_t& a, SeqInfo& sq) {
@@ -3627,7 +3709,9 @@ __device__ __forceinline__ void small_vanilla(cargs_t& a, SeqInfo& sq) {
     for (int c = 0; c < NJ; ++c)
 #pragma unroll
         for (int i = 0; i < KMAX; ++i)
-            col[c][i] = (on[c] && i < K) ? a.Acol[(int64_t)i * a.Kp + lane + 64 * c] : -INFINITY;
+            col[c][i] = (on[c] && i < K) ? a.Acol[(int64_t)i * a.a_pitch + lane + 64 * c] : -INFINITY;
+    int32_t lo[KMAX];
+    small_states(lo);
     float bq[NJ][kSmallPrefetch];
 #pragma unroll
     for (int c = 0; c < NJ; ++c)
@@ -3656,7 +3740,7 @@ __device__ __forceinline__ void small_vanilla(cargs_t& a, SeqInfo& sq) {
         }
         float best[NJ];
         int32_t arg[NJ];
-        small_candidates<KMAX, NJ>(col, d, best, arg);
+        small_candidates<KMAX, NJ>(col, lo, d, best, arg);
 #pragma unroll
         for (int c = 0; c < NJ; ++c) {
             if (on[c]) psi[(int64_t)t * K + lane + 64 * c] = (uint16_t)arg[c];
@@ -3689,16 +3773,9 @@ __device__ __forceinline__ void small_vanilla(cargs_t& a, SeqInfo& sq) {
         *sq.score = sc;
         sq.path[T - 1] = qT;
     }
-    // backtrace from q*_{T-1} by one lane, while the table rows this wave
-    // wrote are still in its XCD's L2 (the finish kernel skips the walk)
-    __syncthreads();
-    if (lane == 0) {
-        int32_t q = qT;
-        for (int32_t t = T - 1; t > 0; --t) {
-            q = clampi(psi[(int64_t)t * K + q], K);
-            sq.path[t - 1] = q;
-        }
-    }
+    // backtrace from q*_{T-1} (the finish kernel skips the walk)
+    __shared__ __align__(16) uint16_t walk[kSmallWalk];
+    small_walk(psi, K, T, qT, sq.path, walk);
 }
 
 // One kernel per width (K <= 32, 64), so each gets the register allocation
@@ -3736,7 +3813,7 @@ __device__ __forceinline__ void small_vanilla_waves(const EngineArgs* __restrict
     const int64_t ld = sq.ld;
     float col[KMAX];
 #pragma unroll
-    for (int i = 0; i < KMAX; ++i) col[i] = (on && i < K) ? a.Acol[(int64_t)i * a.Kp + j] : -INFINITY;
+    for (int i = 0; i < KMAX; ++i) col[i] = (on && i < K) ? a.Acol[(int64_t)i * a.a_pitch + j] : -INFINITY;
     float bq[kSmallPrefetch];
 #pragma unroll
     for (int k = 0; k < kSmallPrefetch; ++k) bq[k] = (on && 1 + k < T) ? lb[(int64_t)(1 + k) * ld + j] : 0.0f;
@@ -3792,12 +3869,9 @@ __device__ __forceinline__ void small_vanilla_waves(const EngineArgs* __restrict
     if (j == 0) {
         *sq.score = sc;
         sq.path[T - 1] = qT;
-        int32_t q = qT;
-        for (int32_t t = T - 1; t > 0; --t) {
-            q = clampi(psi[(int64_t)t * K + q], K);
-            sq.path[t - 1] = q;
-        }
     }
+    __shared__ __align__(16) uint16_t walk[kSmallWalk];
+    small_walk(psi, K, T, qT, sq.path, walk);
 }
 
 extern "C" __global__ __launch_bounds__(128) void fv_small_vanilla128_kernel(const EngineArgs* __restrict__ table) {
@@ -3841,6 +3915,7 @@ struct SmallWave {
     int32_t lane, K;
     bool on[NJ];
     float col[NJ][KMAX];
+    int32_t lo[KMAX];
     float bq[NJ][kSmallPrefetch];
     gfloat_t* lb;
     int64_t ld;
@@ -3865,7 +3940,7 @@ struct SmallWave {
             bq[c][kSmallPrefetch - 1] =
                 (on[c] && t + kSmallPrefetch <= n) ? lb[(int64_t)(t + kSmallPrefetch) * ld + lane + 64 * c] : 0.0f;
         }
-        small_candidates<KMAX, NJ>(col, d, best, arg);
+        small_candidates<KMAX, NJ>(col, lo, d, best, arg);
 #pragma unroll
         for (int c = 0; c < NJ; ++c) d[c] = on[c] ? best[c] + bt[c] : -INFINITY;
     }
@@ -3898,7 +3973,8 @@ __device__ __forceinline__ void small_flash(cargs_t& a, SeqInfo& sq, uint16_t* l
     for (int c = 0; c < NJ; ++c)
 #pragma unroll
         for (int i = 0; i < KMAX; ++i)
-            w.col[c][i] = (w.on[c] && i < K) ? a.Acol[(int64_t)i * a.Kp + lane + 64 * c] : -INFINITY;
+            w.col[c][i] = (w.on[c] && i < K) ? a.Acol[(int64_t)i * a.a_pitch + lane + 64 * c] : -INFINITY;
+    small_states(w.lo);
     int32_t* path = sq.path;
     const int32_t leaf_max = a.leaf_len < kSmallLeafRows ? a.leaf_len : kSmallLeafRows;
     float d0[NJ];
@@ -4006,7 +4082,7 @@ __device__ __forceinline__ void small_flash(cargs_t& a, SeqInfo& sq, uint16_t* l
                     x[c] = d0[c];
                     if (m > 0) {
                         const int32_t j = lane + 64 * c;
-                        const float arow = w.on[c] ? a.Acol[(int64_t)tk.q_prev * a.Kp + j] : -INFINITY;
+                        const float arow = w.on[c] ? a.Acol[(int64_t)tk.q_prev * a.a_pitch + j] : -INFINITY;
                         const float cc = a.relative_init ? arow : tk.alpha + arow;
                         x[c] = w.on[c] ? cc + w.lb[(int64_t)m * w.ld + j] : -INFINITY;
                     }
@@ -4122,7 +4198,7 @@ __device__ __forceinline__ void small_flash_waves(const EngineArgs* __restrict__
     const int32_t leaf_max = a.leaf_len < kSmallLeafRows ? a.leaf_len : kSmallLeafRows;
     float col[KMAX];
 #pragma unroll
-    for (int i = 0; i < KMAX; ++i) col[i] = (on && i < K) ? a.Acol[(int64_t)i * a.Kp + j] : -INFINITY;
+    for (int i = 0; i < KMAX; ++i) col[i] = (on && i < K) ? a.Acol[(int64_t)i * a.a_pitch + j] : -INFINITY;
     const float d0 = on ? (a.log_pi ? a.log_pi[j] + lb[j] : lb[j]) : -INFINITY;
     float* const dsnap = a.root_copy + sq.root_off * (int64_t)a.Kp;                     // [pp-1][Kp]
     int32_t* const link = reinterpret_cast<int32_t*>(dsnap + (int64_t)(pp - 1) * a.Kp);  // [pp-1][Kp]
@@ -4244,7 +4320,7 @@ __device__ __forceinline__ void small_flash_waves(const EngineArgs* __restrict__
                 const int32_t m = tk.m, n = tk.n;
                 float x = d0;
                 if (m > 0) {
-                    const float arow = on ? a.Acol[(int64_t)tk.q_prev * a.Kp + j] : -INFINITY;
+                    const float arow = on ? a.Acol[(int64_t)tk.q_prev * a.a_pitch + j] : -INFINITY;
                     const float cc = a.relative_init ? arow : tk.alpha + arow;
                     x = on ? cc + lb[(int64_t)m * ld + j] : -INFINITY;
                 }

@@ -193,7 +193,8 @@ struct EngineArgs {
     // model
     int32_t K, Kp;
     const float* log_pi;        // may be null
-    const float* Acol;          // the same matrix as the engine's Ap: row-major, pitch Kp
+    const float* Acol;          // the same matrix as the engine's Ap: row-major, pitch a_pitch: Kp, or
+    int32_t a_pitch;            // K where a small model's kernel reads the caller's own
     const float* At;            // its transpose (At[j * Kp + i]), Kp <= kColMaxKp; else null
     // sequences
     SeqInfo* seqs;
