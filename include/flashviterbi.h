@@ -61,7 +61,11 @@ typedef enum {
 
 enum { FV_DENSE = 0, FV_CSR = 1 };
 
-/* Decode flags (bit set).  Placement of the rows in flight: by default the
+/* Decode flags (bit set).  Without flags (FV_FLAG_VALIDATE aside) dense
+ * vanilla and FLASH decodes up to K = 16384, and beams up to B = 256 on CSR
+ * models and dense ones up to K = 2048, run on blocks that take whole tasks;
+ * the flags below that choose among the persistent engine's ways mean the
+ * engine.  Placement of the engine's rows in flight: by default the
  * library keeps each row on one XCD and tiles rows onto lanes (many rows,
  * log A shared through the XCD's L2), or, for large K or very few rows, uses
  * wide rows (every compute unit takes a column slice of every row and log A
@@ -114,8 +118,9 @@ enum { FV_FLAG_RELATIVE_INIT = 1u << 4 };
  * lane tiles (lanes = rows, log A as wave-uniform scalars).
  * FV_FLAG_STEP_ITEMS takes column items instead of slabs; FV_FLAG_STEP_TILES
  * takes lane tiles for any number of rows (they exclude each other).
- * FV_FLAG_ENGINE decodes vanilla and FLASH on a small dense model (K <= 256)
- * with the persistent engine instead of one block per sequence. */
+ * FV_FLAG_ENGINE decodes with the persistent engine whatever the model.
+ * Vanilla and FLASH on small dense models (K <= 256) heed no other choice of
+ * this list. */
 enum { FV_FLAG_STEP_ITEMS = 1u << 5, FV_FLAG_STEP_TILES = 1u << 6, FV_FLAG_ENGINE = 1u << 7 };
 enum { FV_VANILLA = 0, FV_FLASH = 1, FV_BEAM = 2 };
 

@@ -112,7 +112,11 @@ fv_status fv_set_error(fv_status s, const char* fmt, ...) {
 // the array's name to a kernel (on the host it is only a stand-in for the
 // symbol): the device address comes from hipGetSymbolAddress, once per
 // device, and is kept in g_scratch_ptr.
-static __device__ __align__(256) unsigned char scratch[FV_NOALLOC_SCRATCH_BYTES];
+// Beyond FV_NOALLOC_SCRATCH_BYTES it has room for what a bounded decode adds
+// to the lock-step engine's regions (at most 0.4 MB for one sequence), so that
+// the sizes the entry point takes are the engine's.
+constexpr size_t kNoallocExtra = 1 << 20;
+static __device__ __align__(256) unsigned char scratch[FV_NOALLOC_SCRATCH_BYTES + kNoallocExtra];
 
 namespace {
 
@@ -1057,19 +1061,23 @@ fv_status fv_decode_flash_noalloc(const fv_trans* A, const float* log_pi, const 
                                   uint32_t flags, fv_stream_t stream) {
     if (T < 1) return fail(FV_E_INVALID_ARG, "T must be >= 1 (got %d)", T);
     if (P <= 0) P = auto_parallelism(&T, 1);
-    size_t need = 0;
-    fv_status rc = fv_workspace_size(FV_FLASH, A, 1, &T, nullptr, 1, P, 0, &need);
+    BatchPlan bp;
+    fv_status rc = plan_batch(FV_FLASH, A, 1, &T, nullptr, 1, P, 0, true, bp);
     if (rc != FV_OK) return rc;
+    size_t extra = 0;   // regions of a bounded decode
+    for (const DenseLayout& L : bp.L)
+        for (const Region& r : {L.cmax, L.rowb, L.xch}) extra += (r.bytes + kAlign - 1) / kAlign * kAlign;
+    const size_t need = bp.total - std::min(extra, kNoallocExtra);
     if (need > (size_t)FV_NOALLOC_SCRATCH_BYTES)
         return fail(FV_E_WORKSPACE,
                     "fv_decode_flash_noalloc: this decode needs %zu bytes of scratch; the fixed scratch holds %zu "
                     "(use fv_decode_flash with a workspace)",
-                    need, (size_t)FV_NOALLOC_SCRATCH_BYTES);
+                    bp.total, (size_t)FV_NOALLOC_SCRATCH_BYTES);
     void* ws = nullptr;
     rc = scratch_address(&ws);
     if (rc != FV_OK) return rc;
     return decode_one(FV_FLASH, A, log_pi, log_b, ld, T, P, 0, path, score, status, flags, ws,
-                      (size_t)FV_NOALLOC_SCRATCH_BYTES, stream);
+                      (size_t)FV_NOALLOC_SCRATCH_BYTES + kNoallocExtra, stream);
 }
 
 fv_status fv_decode_beam(const fv_trans* A, const float* log_pi, const float* log_b, int64_t ld, int32_t T,

@@ -106,7 +106,7 @@ def decode(log_a, log_b: torch.Tensor, log_pi: torch.Tensor | None = None,
     tables; same results).  relative_init: subtasks start from the paper's
     displayed initialisation (the carried score dropped; dense models; paths
     may differ from vanilla's at near ties).  step ("auto", "items", "tiles")
-    and engine (True: the persistent engine even for K <= 256) choose kernels
+    and engine (True: the persistent engine whatever the model) choose kernels
     for tuning; results are the same.  Returns (path int32 [T], score
     float32 [1], status int32 [1]) on the device."""
     model, K, dev = _model(log_a)
@@ -244,9 +244,7 @@ def decode_batch(log_a, batch: Batch, log_pi=None, method: str = "flash", P: int
                  ws: torch.Tensor | None = None, rows: str = "auto", validate: bool = False,
                  leaves: bool = True, relative_init: bool = False, step: str = "auto", engine: bool = False,
                  emission=None):
-    """Decode all sequences of `batch` in one decode launch (the persistent
-    engine, or one block per sequence for vanilla and FLASH when every dense
-    model has K <= 256).  log_a: a
+    """Decode all sequences of `batch` in one call.  log_a: a
     dense [K, K] tensor or a CsrModel, or a list of them when the batch's
     sequences use several models (batch.models indexes it); log_pi: a [K]
     tensor or None, or a list matching log_a.  Results land in batch.paths
