@@ -71,7 +71,7 @@ constexpr int kRowCap = 128;          // rows of a wave's lists (FILTER)
 // Equal scores are decided by the low word: the smaller one is the larger
 // number for negative scores, the larger one for positive scores, so the
 // state is stored as itself while scores are negative and complemented while
-// they are positive (team_finish handles columns of the other sign, and zeros).
+// they are positive (`finish` handles columns of the other sign, and zeros).
 struct BoundEnt {
     int32_t lo;
     float v;
@@ -91,7 +91,8 @@ struct TeamLds {
             BoundEnt rows[FILTER ? 16 : 1][2][FILTER ? kRowCap + 16 : 1];   // a wave's rows to read, by half of its group
             float eb[2][NB * TC];       // emission rows of the block's columns: in use, and coming
         };
-        uint32_t walk[(8 * (FILTER ? 1 : kTiers) * LC + (FILTER ? 256 * (kRowCap + 16) : 16) + 8 * NB * TC) / 4];   // backpointer rows being walked
+        // backpointer rows being walked
+        uint32_t walk[(8 * (FILTER ? 1 : kTiers) * LC + (FILTER ? 256 * (kRowCap + 16) : 16) + 8 * NB * TC) / 4];
     };
     unsigned long long part[FILTER ? 1 : TC];   // order keys of partial maxima
     uint32_t rb[FILTER ? 16 * KC : 1];   // [groups, Kp] row bounds of both halves
@@ -203,7 +204,6 @@ template <int KC, int LC, int NB, bool TEAM, int W, bool FILTER>
 __device__ __forceinline__ void team_decode(cargs_t& a) {
     constexpr int kTThreads = 64 * W;
     constexpr int TC = TeamLds<KC, LC, NB, TEAM, FILTER>::TC;
-    constexpr int GPW = 1;   // groups of a wave, at most
     constexpr int UN = KC <= 256 ? 16 : 8;   // list entries of a unit of work
     constexpr int UL = UN / 4;               // 16 lanes across 64 columns: 4 entries side by side
     // long rows: the groups' maxima are polled first, the words then read once
@@ -230,17 +230,11 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
     int32_t wpg = W;
     if (FILTER) wpg = 1;
     while (wpg > 1 && wpg * ngl > W) wpg >>= 1;
-    const int32_t g0 = wv / wpg, sub = wv - g0 * wpg;             // this wave's (first) group and share of it
+    const int32_t g = wv / wpg, sub = wv - g * wpg;               // this wave's group and share of it
     const int32_t lc4 = 4 * (lane & 15);
-    int32_t g = g0;                                               // the group being worked on, and
     // the column (in the block) a lane ends with
-    int32_t jl = g * 64 + (FILTER ? 4 * (lane & 8) + 4 * (lane & 7) : lc4) + (lane >> 4);
-    bool active = g < ngl;
-    auto at_group = [&](int32_t k) {                              // this wave's k-th group
-        g = g0 + k * W;
-        if (!FILTER) jl = g * 64 + lc4 + (lane >> 4);
-        active = g < ngl;
-    };
+    const int32_t jl = g * 64 + (FILTER ? 4 * (lane & 8) + 4 * (lane & 7) : lc4) + (lane >> 4);
+    const bool active = g < ngl;
     for (int32_t k = tid; k < TC; k += kTThreads) {
         const float c = k < cn ? score_of_key(a.cmax[cb + k]) : -INFINITY;
         s.cm[k] = c > -INFINITY ? c : __builtin_nanf("");
@@ -425,9 +419,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             s.cnt[tid][0] = s.cnt[tid][1] = s.cnt[tid][2] = s.cnt[tid][3] = 0;
         }
         __syncthreads();
-        for (int k = 0; k < GPW; ++k) {
-            if (GPW > 1) at_group(k);
-            if (!active || sub != 0) break;
+        if (active && sub == 0) {
             float x = -INFINITY;
             if (jl < cn) {
                 const int32_t j = cb + jl;
@@ -510,62 +502,62 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             // wave has its own group and looks at the bound, what most of them need
             float h0, h1, h2;
             for (int32_t go = 0;; ++go) {
-            const float gx = (step == 0 ? G1 : G) * __int_as_float((127 - go) << 23);
-            h0 = D - (FILTER ? kNear : (wpg > 1 || KC <= 256 ? 1.0f : 0.75f)) * gx;
-            h1 = D - (FILTER ? kFar : (wpg > 1 || KC <= 256 ? 1.2f : 1.0f)) * gx;
-            h2 = FILTER ? h1 : D - (GATE ? 1.4f : (wpg > 1 || KC <= 256 ? 1.7f : 1.35f)) * gx;
+                const float gx = (step == 0 ? G1 : G) * __int_as_float((127 - go) << 23);
+                h0 = D - (FILTER ? kNear : (wpg > 1 || KC <= 256 ? 1.0f : 0.75f)) * gx;
+                h1 = D - (FILTER ? kFar : (wpg > 1 || KC <= 256 ? 1.2f : 1.0f)) * gx;
+                h2 = FILTER ? h1 : D - (GATE ? 1.4f : (wpg > 1 || KC <= 256 ? 1.7f : 1.35f)) * gx;
 #pragma unroll
-            for (int c = 0; c < NS; c += CN) {
-                if (c * kTThreads >= K) break;
-                float x[CN];
-                if constexpr (TEAM) {
-                    if constexpr (GATE) poll(c);
+                for (int c = 0; c < NS; c += CN) {
+                    if (c * kTThreads >= K) break;
+                    float x[CN];
+                    if constexpr (TEAM) {
+                        if constexpr (GATE) poll(c);
+#pragma unroll
+                        for (int k = 0; k < CN; ++k) {
+                            const int32_t i = tid + (c + k) * kTThreads;
+                            x[k] = i < K ? __uint_as_float((uint32_t)v[k]) : -INFINITY;
+                            if (i < K && mode == BM_DIV) s.anc[0][i] = (uint16_t)(v[k] >> 32);
+                        }
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < CN; ++k) {
+                            const int32_t i = tid + (c + k) * kTThreads;
+                            x[k] = i < K ? s.x[xp][i] : -INFINITY;
+                        }
+                    }
 #pragma unroll
                     for (int k = 0; k < CN; ++k) {
-                        const int32_t i = tid + (c + k) * kTThreads;
-                        x[k] = i < K ? __uint_as_float((uint32_t)v[k]) : -INFINITY;
-                        if (i < K && mode == BM_DIV) s.anc[0][i] = (uint16_t)(v[k] >> 32);
-                    }
-                } else {
-#pragma unroll
-                    for (int k = 0; k < CN; ++k) {
-                        const int32_t i = tid + (c + k) * kTThreads;
-                        x[k] = i < K ? s.x[xp][i] : -INFINITY;
+                        const bool fin = x[k] > -INFINITY;
+                        const uint64_t c0 = __builtin_amdgcn_ballot_w64(fin && x[k] >= h0);
+                        const uint64_t c1 = __builtin_amdgcn_ballot_w64(fin && x[k] >= h1);
+                        const uint64_t c2 = __builtin_amdgcn_ballot_w64(fin && x[k] >= h2);
+                        if (__builtin_amdgcn_ballot_w64(fin) & ~c2)
+                            if (lane == 0) s.cnt[par][3] = 1;
+                        if (c2 == 0) continue;
+                        const int32_t n0 = __popcll(c0), n1 = __popcll(c1) - n0, n2 = __popcll(c2) - n0 - n1;
+                        const int32_t add = lane == 0 ? n0 : (lane == 1 ? n1 : n2);
+                        int32_t at = 0;
+                        if (lane < kTiers) at = atomicAdd(&s.cnt[par][lane], add);
+                        const int32_t a0 = __builtin_amdgcn_readlane(at, 0), a1 = __builtin_amdgcn_readlane(at, 1),
+                                      a2 = __builtin_amdgcn_readlane(at, 2);
+                        const int32_t l = x[k] >= h0 ? 0 : (x[k] >= h1 ? 1 : 2);
+                        const uint64_t my = l == 0 ? c0 : (l == 1 ? c1 & ~c0 : c2 & ~c1);
+                        const int32_t pos = (l == 0 ? a0 : (l == 1 ? a1 : a2)) +
+                                            __builtin_amdgcn_mbcnt_hi((uint32_t)(my >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((uint32_t)my, 0));
+                        if (fin && x[k] >= h2 && (LC >= KC || pos < LC))
+                            s.list[FILTER ? 0 : l][FILTER && l ? LC - 1 - pos : pos] =
+                                BoundEnt{(tid + (c + k) * kTThreads) ^ flip, x[k]};
                     }
                 }
-#pragma unroll
-                for (int k = 0; k < CN; ++k) {
-                    const bool fin = x[k] > -INFINITY;
-                    const uint64_t c0 = __builtin_amdgcn_ballot_w64(fin && x[k] >= h0);
-                    const uint64_t c1 = __builtin_amdgcn_ballot_w64(fin && x[k] >= h1);
-                    const uint64_t c2 = __builtin_amdgcn_ballot_w64(fin && x[k] >= h2);
-                    if (__builtin_amdgcn_ballot_w64(fin) & ~c2)
-                        if (lane == 0) s.cnt[par][3] = 1;
-                    if (c2 == 0) continue;
-                    const int32_t n0 = __popcll(c0), n1 = __popcll(c1) - n0, n2 = __popcll(c2) - n0 - n1;
-                    const int32_t add = lane == 0 ? n0 : (lane == 1 ? n1 : n2);
-                    int32_t at = 0;
-                    if (lane < kTiers) at = atomicAdd(&s.cnt[par][lane], add);
-                    const int32_t a0 = __builtin_amdgcn_readlane(at, 0), a1 = __builtin_amdgcn_readlane(at, 1),
-                                  a2 = __builtin_amdgcn_readlane(at, 2);
-                    const int32_t l = x[k] >= h0 ? 0 : (x[k] >= h1 ? 1 : 2);
-                    const uint64_t my = l == 0 ? c0 : (l == 1 ? c1 & ~c0 : c2 & ~c1);
-                    const int32_t pos = (l == 0 ? a0 : (l == 1 ? a1 : a2)) +
-                                        __builtin_amdgcn_mbcnt_hi((uint32_t)(my >> 32),
-                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)my, 0));
-                    if (fin && x[k] >= h2 && (LC >= KC || pos < LC))
-                        s.list[FILTER ? 0 : l][FILTER && l ? LC - 1 - pos : pos] =
-                            BoundEnt{(tid + (c + k) * kTThreads) ^ flip, x[k]};
-                }
-            }
-            if (LC >= KC || go == 8) break;
-            // a first list beyond its room: a shorter reach
-            __syncthreads();
-            const bool fits = s.cnt[par][0] <= LC;
-            __syncthreads();
-            if (fits) break;
-            if (tid < 4) s.cnt[par][tid] = 0;
-            __syncthreads();
+                if (LC >= KC || go == 8) break;
+                // a first list beyond its room: a shorter reach
+                __syncthreads();
+                const bool fits = s.cnt[par][0] <= LC;
+                __syncthreads();
+                if (fits) break;
+                if (tid < 4) s.cnt[par][tid] = 0;
+                __syncthreads();
             }
             if (wpg > 1)
                 for (int32_t k = tid; k < TC; k += kTThreads) s.part[k] = 0;
@@ -789,8 +781,10 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                                 for (int c = 0; c < 4; ++c) {
                                     if (c < from || !room) continue;
                                     const float y0 = add_lo16(x[c], r[c]), y1 = add_hi16(x[c], r[c]);
-                                    const uint64_t m0 = __builtin_amdgcn_ballot_w64(y0 >= lo0) & __builtin_amdgcn_ballot_w64(y0 < hi0);
-                                    const uint64_t m1 = __builtin_amdgcn_ballot_w64(y1 >= lo1) & __builtin_amdgcn_ballot_w64(y1 < hi1);
+                                    const uint64_t m0 = __builtin_amdgcn_ballot_w64(y0 >= lo0) &
+                                                        __builtin_amdgcn_ballot_w64(y0 < hi0);
+                                    const uint64_t m1 = __builtin_amdgcn_ballot_w64(y1 >= lo1) &
+                                                        __builtin_amdgcn_ballot_w64(y1 < hi1);
                                     const int32_t a0 = n0 + __popcll(m0), a1 = n1 + __popcll(m1);
                                     room = max(a0, a1) <= kRowCap;
                                     if (!room) continue;
@@ -848,113 +842,106 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     else F = fmaxf(F + kEma * (u - F), 1e-4f);
                     finish(top, thr, 0, more, 0.0f, 0);
                 }
-            } else
-#pragma unroll 1
-            for (int gi = 0; gi < GPW; ++gi) {
-            if (GPW > 1) {
-                at_group(gi);
-                if (!active && wpg == 1) break;
-            }
-            double best[4] = {none, none, none, none};
-            const int32_t add = (g * 64 + lc4) * 4 + add0;
-            // the waves of a group share its first lists (the first alone when
-            // the group is one wave's) without a look at the bound
-            int32_t k = 0;
-            if (active) {
-                for (; k < min(wpg > 1 ? 2 : 1, lists); ++k) {
-                    const BoundEnt* const list = s.list[k];
-                    const int32_t cnt = uni(s.cnt[par][k]), inc = wpg * UN;
-                    BoundEnt e0[UL], e1[UL];
-                    vec_t v0[UL], v1[UL];
-                    int32_t e = sub * UN;
-                    if (e >= cnt) continue;
-                    load(e0, v0, list, e, cnt, add);
-                    for (; e + 2 * inc < cnt; e += 2 * inc) {
-                        load(e1, v1, list, e + inc, cnt, add);
-                        scan(best, e0, v0);
-                        load(e0, v0, list, e + 2 * inc, cnt, add);
-                        scan(best, e1, v1);
-                    }
-                    if (e + inc < cnt) {
-                        load(e1, v1, list, e + inc, cnt, add);
-                        scan(best, e0, v0);
-                        scan(best, e1, v1);
-                    } else {
-                        scan(best, e0, v0);
-                    }
-                }
-            }
-            k = min(wpg > 1 ? 2 : 1, lists);
-            double top = merge_group(best);
-            if (wpg > 1) {
-                if (active) atomicMax(&s.part[jl], pattern_key(top));
-                __syncthreads();
-                if (active) top = pattern_of_key(s.part[jl]);
-            }
-            if (active && sub == 0) {
-                // true when nothing outside the first k lists can win a column
-                auto closed = [&]() {
-                    return __builtin_amdgcn_ballot_w64(below(k) + s.cm[jl] >= __int_as_float(__double2hiint(top))) == 0;
-                };
-                bool stop = k > 0 && closed();
-                while (!stop && k < lists) {
-                    const int32_t cnt = uni(s.cnt[par][k]);
-                    double more[4] = {none, none, none, none};
-                    for (int32_t e = 0; e < cnt; e += 2 * UN) {
-                        BoundEnt e0[2 * UL];
-                        vec_t v0[2 * UL];
-                        load(e0, v0, s.list[k], e, cnt, add);
-                        scan(more, e0, v0);
-                    }
-                    ++k;
-                    top = max64(top, merge_group(more));
-                    stop = closed();
-                }
-                // states outside the lists, where the bound still asks for them
-                const bool out = !stop && outside;
-                float fo = -INFINITY;
-                int32_t qo = 0;
-                if (out) {
-                    // none that scores below thr can win (checked, not derived: the
-                    // subtraction is rounded)
-                    const float bs = __int_as_float(__double2hiint(top)), cm = s.cm[jl];
-                    const float nd = D - (bs - cm);
-                    const float lim = __uint_as_float(wave_max(nd > 0.0f ? __float_as_uint(nd) : 0u));
-                    float thr = D - lim * 1.001f - 1e-6f * fabsf(D);
-                    if (__builtin_amdgcn_ballot_w64(cm == cm && !(thr + cm < bs))) thr = -FLT_MAX;
-                    const float top_of = below(k);
-                    gfloat_t* const ak = as_global(a.Acol) + cb + jl;
-                    for (int32_t c0 = 0; c0 < K; c0 += 256) {
-                        float xo[4];
-#pragma unroll
-                        for (int u = 0; u < 4; ++u)
-                            xo[u] = score_at(min(c0 + u * 64 + lane, K - 1));
-#pragma unroll
-                        for (int u = 0; u < 4; ++u) {
-                            const bool in = c0 + u * 64 + lane < K && xo[u] >= thr && xo[u] < top_of;
-                            uint64_t mask = __builtin_amdgcn_ballot_w64(in);
-                            while (mask) {   // four rows in flight
-                                int32_t r[4];
-                                float v[4];
-#pragma unroll
-                                for (int q = 0; q < 4; ++q) {
-                                    r[q] = mask ? (int32_t)__builtin_ctzll(mask) : r[q ? q - 1 : 0];
-                                    mask &= mask - 1;
-                                    v[q] = ak[(uint32_t)(c0 + u * 64 + r[q]) * (uint32_t)Kp];
-                                }
-#pragma unroll
-                                for (int q = 0; q < 4; ++q)
-                                    take1(fo, qo,
-                                          __int_as_float(__builtin_amdgcn_readlane(__float_as_int(xo[u]), r[q])) + v[q],
-                                          c0 + u * 64 + r[q]);
-                            }
+            } else {
+                double best[4] = {none, none, none, none};
+                const int32_t add = (g * 64 + lc4) * 4 + add0;
+                // the waves of a group share its first lists (the first alone when
+                // the group is one wave's) without a look at the bound
+                int32_t k = 0;
+                if (active) {
+                    for (; k < min(wpg > 1 ? 2 : 1, lists); ++k) {
+                        const BoundEnt* const list = s.list[k];
+                        const int32_t cnt = uni(s.cnt[par][k]), inc = wpg * UN;
+                        BoundEnt e0[UL], e1[UL];
+                        vec_t v0[UL], v1[UL];
+                        int32_t e = sub * UN;
+                        if (e >= cnt) continue;
+                        load(e0, v0, list, e, cnt, add);
+                        for (; e + 2 * inc < cnt; e += 2 * inc) {
+                            load(e1, v1, list, e + inc, cnt, add);
+                            scan(best, e0, v0);
+                            load(e0, v0, list, e + 2 * inc, cnt, add);
+                            scan(best, e1, v1);
+                        }
+                        if (e + inc < cnt) {
+                            load(e1, v1, list, e + inc, cnt, add);
+                            scan(best, e0, v0);
+                            scan(best, e1, v1);
+                        } else {
+                            scan(best, e0, v0);
                         }
                     }
-                    top = max64(top, __hiloint2double(__float_as_int(fo), qo ^ flip));
                 }
-                finish(top, 0.0f, k, out, fo, qo);
-            }
-            if (wpg > 1) break;
+                k = min(wpg > 1 ? 2 : 1, lists);
+                double top = merge_group(best);
+                if (wpg > 1) {
+                    if (active) atomicMax(&s.part[jl], pattern_key(top));
+                    __syncthreads();
+                    if (active) top = pattern_of_key(s.part[jl]);
+                }
+                if (active && sub == 0) {
+                    // true when nothing outside the first k lists can win a column
+                    auto closed = [&]() {
+                        return __builtin_amdgcn_ballot_w64(below(k) + s.cm[jl] >= __int_as_float(__double2hiint(top))) == 0;
+                    };
+                    bool stop = k > 0 && closed();
+                    while (!stop && k < lists) {
+                        const int32_t cnt = uni(s.cnt[par][k]);
+                        double more[4] = {none, none, none, none};
+                        for (int32_t e = 0; e < cnt; e += 2 * UN) {
+                            BoundEnt e0[2 * UL];
+                            vec_t v0[2 * UL];
+                            load(e0, v0, s.list[k], e, cnt, add);
+                            scan(more, e0, v0);
+                        }
+                        ++k;
+                        top = max64(top, merge_group(more));
+                        stop = closed();
+                    }
+                    // states outside the lists, where the bound still asks for them
+                    const bool out = !stop && outside;
+                    float fo = -INFINITY;
+                    int32_t qo = 0;
+                    if (out) {
+                        // none that scores below thr can win (checked, not derived: the
+                        // subtraction is rounded)
+                        const float bs = __int_as_float(__double2hiint(top)), cm = s.cm[jl];
+                        const float nd = D - (bs - cm);
+                        const float lim = __uint_as_float(wave_max(nd > 0.0f ? __float_as_uint(nd) : 0u));
+                        float thr = D - lim * 1.001f - 1e-6f * fabsf(D);
+                        if (__builtin_amdgcn_ballot_w64(cm == cm && !(thr + cm < bs))) thr = -FLT_MAX;
+                        const float top_of = below(k);
+                        gfloat_t* const ak = as_global(a.Acol) + cb + jl;
+                        for (int32_t c0 = 0; c0 < K; c0 += 256) {
+                            float xo[4];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+                                xo[u] = score_at(min(c0 + u * 64 + lane, K - 1));
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                const bool in = c0 + u * 64 + lane < K && xo[u] >= thr && xo[u] < top_of;
+                                uint64_t mask = __builtin_amdgcn_ballot_w64(in);
+                                while (mask) {   // four rows in flight
+                                    int32_t r[4];
+                                    float v[4];
+#pragma unroll
+                                    for (int q = 0; q < 4; ++q) {
+                                        r[q] = mask ? (int32_t)__builtin_ctzll(mask) : r[q ? q - 1 : 0];
+                                        mask &= mask - 1;
+                                        v[q] = ak[(uint32_t)(c0 + u * 64 + r[q]) * (uint32_t)Kp];
+                                    }
+#pragma unroll
+                                    for (int q = 0; q < 4; ++q)
+                                        take1(fo, qo,
+                                              __int_as_float(__builtin_amdgcn_readlane(__float_as_int(xo[u]), r[q])) + v[q],
+                                              c0 + u * 64 + r[q]);
+                                }
+                            }
+                        }
+                        top = max64(top, __hiloint2double(__float_as_int(fo), qo ^ flip));
+                    }
+                    finish(top, 0.0f, k, out, fo, qo);
+                }
             }
             if (t == e_next) {
                 e_prev = t;
