@@ -24,12 +24,14 @@
 // (rounded up to float16; in LDS), delta_i + log A(i, j) <= (delta_i + r_i) +
 // cm_j, and states with fl(delta_i + r_i) < h lose where fl(h + cm_j) <
 // best_j.  h follows what the half group's last steps needed; where the
-// results do not close the bound it takes h from them and reads the rest,
-// once.  Of K = 1024 with Dirichlet(0.1) transitions a half group then reads
-// about 65 rows of 128 bytes instead of 200 of 256: 256 sequences, T ~ U[500,
-// 8000], FLASH P = 64: 111.5 -> 88.3 ms.  Where several waves share a group
-// (teams) the filter's own steps take longer than the rows it saves (K = 512,
-// one sequence: 2.0 -> 2.6 ms; 64 sequences of K = 1000: 13.3 -> 17.3 ms).
+// results do not close the bound it takes h from them and reads the rest:
+// the listed states from the new h on, and of the states on no list (a bound is
+// no larger than its state's score) those that may still win.  Of
+// K = 1024 with Dirichlet(0.1) transitions a half group then reads about 65
+// rows of 128 bytes instead of 200 of 256: 256 sequences, T ~ U[500, 8000],
+// FLASH P = 64: 111.5 -> 88.3 ms.  Where several waves share a group (teams)
+// the filter's own steps take longer than the rows it saves (K = 512, one
+// sequence: 2.0 -> 2.6 ms; 64 sequences of K = 1000: 13.3 -> 17.3 ms).
 //
 // Work division.  A team of M blocks decodes one task (a vanilla pass, a FLASH
 // root, a FLASH segment); each block owns up to kTeamGroups groups of 64
@@ -579,7 +581,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             const int4 cn4 = *reinterpret_cast<const int4*>(s.cnt[par]);
             if constexpr (FILTER) lists = 2;
             if constexpr (LC < KC) lists = uni(cn4.x) > LC ? 0 : (uni(cn4.y) > LC ? 1 : (uni(cn4.z) > LC ? 2 : 3));
-            const bool outside = uni(cn4.w) != 0 || lists < kTiers;
+            const bool outside = uni(cn4.w) != 0 || (!FILTER && lists < kTiers);
             // above every score outside the first n lists
             auto below = [&](int32_t n) { return n == 0 ? INFINITY : (n == 1 ? h0 : (n == 2 ? h1 : h2)); };
             // ---- scan of the groups' columns
@@ -817,23 +819,27 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     float lo = fmaxf(h0, D - kHalf * (step == 0 ? F1 : F)), hi = INFINITY;
                     double top;
                     float u;
-                    bool more = false;
 #pragma unroll 1
                     for (int round = 0;; ++round) {
                         filter(lo, hi, __builtin_amdgcn_ballot_w64(lo < h0) ? 2 : 1);
                         top = merge_halves(b0, b1);
-                        more = open(lo, top);
                         u = reach(top);
-                        if (!more || round == 1) break;
-                        // no row whose bound is below the next lo can win (checked, not derived)
+                        if (round == 2 || !open(lo, top)) break;
+                        // no row whose bound is below the next lo can win (checked, not
+                        // derived), or every listed row with an edge is read; at first
+                        // the rows with bounds from h1 on, which mostly close it
                         hi = lo;
                         lo = fminf(lo, D - u * 1.001f - 1e-6f * fabsf(D));
                         const bool bad = cm == cm && !(lo + cm < __int_as_float(__double2hiint(top)));
-                        if (half_max(bad ? 1u : 0u) || lo < h1) lo = h1;
+                        if (half_max(bad ? 1u : 0u)) lo = -FLT_MAX;
+                        if (round == 0) lo = fmaxf(lo, h1);
                     }
                     float thr = fminf(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(lo), 0)),
                                       __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lo), 8)));
-                    if (more && outside) {
+                    // a bound is no larger than its state's score: below h1 there may
+                    // be states on no list with bounds from lo on
+                    const bool more = thr < h1 && outside && open(h1, top);
+                    if (more) {
                         thr = h1;
                         top = beyond(top, thr);
                         u = reach(top);
