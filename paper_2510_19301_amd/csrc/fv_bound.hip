@@ -1173,7 +1173,11 @@ extern "C" __global__ __launch_bounds__(kBlock) void fv_rowbound_kernel(const fl
         const int32_t i = i0 + r;
         float v = -INFINITY;
         // rounded towards zero, that is, up: the difference is not positive
-        if (i < K && cm > -INFINITY) v = (Ap[(int64_t)i * Kp + j] - cm) * (1.0f - 0x1p-20f);
+        if (i < K && cm > -INFINITY) {
+            const float x = Ap[(int64_t)i * Kp + j];
+            v = (x - cm) * (1.0f - 0x1p-20f);
+            if (x > -INFINITY) v = fmaxf(v, -FLT_MAX);   // an edge, whatever the difference
+        }
         part[r][c] = v;
     }
     __syncthreads();

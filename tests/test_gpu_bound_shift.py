@@ -80,3 +80,24 @@ def test_spread_changes(K, kind, n):
             assert np.float32(so).view(np.uint32) == scores[b].view(np.uint32), (b, T, so, scores[b])
             assert status[b] == rc
             np.testing.assert_array_equal(paths[b][:T], po)
+
+
+def test_edges_at_the_end_of_the_range():
+    """An edge whose distance to its column's maximum is no float."""
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    import paper_2510_19301_amd as fv
+    K, n = 600, 200
+    la = np.full((K, K), -np.inf, np.float32)
+    la[0], la[1], la[5] = -3.39e38, -3.38e38, 2e36
+    lp = np.full(K, -np.inf, np.float32)
+    lp[0], lp[1] = -1e36, -2.1e36               # state 0 wins every column, state 5 is never reached
+    lb = np.zeros((2, K), np.float32)
+    po, so, rc = oracle.vanilla(lp, la, lb)
+    assert rc == fv.FV_OK and po[0] == 0
+    dev = lambda x: torch.from_numpy(x).cuda()
+    batch = fv.Batch([dev(lb)] * n)
+    fv.decode_batch(dev(la), batch, dev(lp), method="vanilla")
+    torch.cuda.synchronize()
+    assert (batch.scores.cpu().numpy() == so).all()
+    assert (batch.paths.cpu().numpy() == po).all()
