@@ -119,8 +119,8 @@ enum { FV_FLAG_RELATIVE_INIT = 1u << 4 };
  * FV_FLAG_STEP_ITEMS takes column items instead of slabs; FV_FLAG_STEP_TILES
  * takes lane tiles for any number of rows (they exclude each other).
  * FV_FLAG_ENGINE decodes with the persistent engine whatever the model.
- * Vanilla and FLASH on small dense models (K <= 256) heed no other choice of
- * this list. */
+ * Vanilla and FLASH calls whose models are all dense with K <= 256 heed no
+ * other choice of this list. */
 enum { FV_FLAG_STEP_ITEMS = 1u << 5, FV_FLAG_STEP_TILES = 1u << 6, FV_FLAG_ENGINE = 1u << 7 };
 enum { FV_VANILLA = 0, FV_FLASH = 1, FV_BEAM = 2 };
 

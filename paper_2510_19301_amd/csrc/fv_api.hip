@@ -499,14 +499,15 @@ struct BoundPlan {
     int64_t scratch = 0;
 };
 
-BoundPlan plan_bounded(uint32_t flags, int32_t method, const fv_trans* A, const DenseLayout& L, const DeviceInfo& di) {
+// per_seq: every model of the call is decoded on one block per sequence.
+BoundPlan plan_bounded(uint32_t flags, bool per_seq, int32_t method, const fv_trans* A, const DenseLayout& L,
+                       const DeviceInfo& di) {
     BoundPlan b;
-    // flags that ask for a placement, a kernel or the full bisection, and
-    // the engine's own hooks, mean the lock-step engine
-    // (which small models' block per sequence has no part in)
+    // flags that ask for a placement, a kernel, the full bisection or the
+    // relative start, and the engine's own hooks, mean the lock-step engine
+    // (which calls with small models alone have no part in)
     if (!L.teams || (flags & FV_FLAG_ENGINE)) return b;
-    if (A->K > kBoundSmallK && ((flags & ~(uint32_t)FV_FLAG_VALIDATE) || g_dbg_max_steps ||
-                                g_dbg_spin_limit || g_dbg_trace))
+    if (!per_seq && ((flags & ~(uint32_t)FV_FLAG_VALIDATE) || g_dbg_max_steps || g_dbg_spin_limit || g_dbg_trace))
         return b;
     // the blocks of the teams wait for each other: all of them are resident
     const int32_t resident = di.cus * di.team_blocks_per_cu[team_kernel(A->K, L.team)];
@@ -688,10 +689,13 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
     // Bisections to the paper's minimum stay here up to K = 256: bounded FLASH
     // passes end in leaves.
     const int32_t small_k = flags & (FV_FLAG_RELATIVE_INIT | FV_FLAG_NO_LEAVES) ? kSmallFlashK : kSmallK;
-    bool small = !(flags & FV_FLAG_ENGINE);
+    // Where every model is dense with K <= kBoundSmallK, the others' flags and
+    // hooks choose nothing: relative starts and full bisections are all `small`.
+    bool small = !(flags & FV_FLAG_ENGINE), per_seq = small;
     for (size_t p = 0; p < bp.L.size(); ++p) {
         const int32_t K_ = bp.L[p].K;
-        small = small && models[bp.model[p]].kind == FV_DENSE &&
+        per_seq = per_seq && models[bp.model[p]].kind == FV_DENSE && bp.method[p] != FV_BEAM && K_ <= kBoundSmallK;
+        small = small && per_seq &&
                 ((bp.method[p] == FV_VANILLA && K_ <= kSmallK) || (bp.method[p] == FV_FLASH && K_ <= small_k));
     }
     bool engine = false;   // the lock-step engine is launched
@@ -701,7 +705,7 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         if (bp.method[p] == FV_BEAM && !(flags & ~(uint32_t)FV_FLAG_VALIDATE) && !g_dbg_max_steps && !g_dbg_spin_limit &&
             !g_dbg_trace && std::min(B, A->K) <= kBeamBlockB && (A->kind == FV_CSR || A->K <= kBeamBlockK))
             beams[p] = di.cus * std::max(1, di.beam_blocks_per_cu[A->kind == FV_CSR ? 1 : 0]);
-        bounds[p] = plan_bounded(flags, bp.method[p], &models[bp.model[p]], bp.L[p], di);
+        bounds[p] = plan_bounded(flags, per_seq, bp.method[p], &models[bp.model[p]], bp.L[p], di);
         engine = engine || bounds[p].teams == 0 || bounds[p].rows > 0;
     }
     for (size_t p = 0; p < bp.L.size(); ++p) {
