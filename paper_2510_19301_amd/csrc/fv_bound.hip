@@ -438,6 +438,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             e_next = w > 2 ? div_end(1) : -1;
         }
         bool retry = false;
+        int32_t made = len;   // positions whose scores the team published
         for (int32_t t = m + 1; t <= n; ++t) {
             const int32_t step = t - m - 1, row = step % NB, half = (step / NB) & 1, par = step & 1;
             const uint32_t tag = (epoch + (uint32_t)step) & kTagBits;
@@ -569,6 +570,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             __syncthreads();
             if (quit) {   // its scans mostly leave the lists: the bound does not prune this
                 retry = true;                   // input, and the engine's step costs the same whatever the scores
+                made = step + 1;                // (every block stops here: the mark came with this row)
                 break;
             }
             if (row == 0) {
@@ -964,7 +966,10 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         const int32_t xe = (int32_t)(epoch + (uint32_t)(n - m)) & 1;   // the last scores' parity
-        epoch += (uint32_t)(len + 1 + (len == 1));   // both parities' words are rewritten by any two tasks
+        // The next tags follow those of the last words written, also where the
+        // pass was given up: what is still there of either parity is a few tags
+        // back, and the tags (15 bits) come round to it in no wait.
+        epoch += (uint32_t)(made + 1 + (made == 1));
         if (M > 1) {
             if (member != 0) {
                 if (tid == 0) st_c(tb.done + member, task_no);

@@ -101,3 +101,30 @@ def test_edges_at_the_end_of_the_range():
     torch.cuda.synchronize()
     assert (batch.scores.cpu().numpy() == so).all()
     assert (batch.paths.cpu().numpy() == po).all()
+
+
+@pytest.mark.parametrize("T", [32770, 32775, 32782, 32783, 32784])
+def test_tasks_after_one_given_up(T):
+    """A long sequence that the bound does not prune (given up after some steps)
+    and short ones that its team takes next: the scores' tags have 15 bits."""
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    import paper_2510_19301_amd as fv
+    K, n = 2100, 200
+    r = np.random.default_rng(T)
+    lbs = [(2 * r.standard_normal((t, K))).astype(np.float32) for t in (5, 12, 24)]
+    la = np.zeros((K, K), np.float32)
+    refs = [oracle.vanilla(None, la, lb) for lb in lbs]
+    dev = lambda x: torch.from_numpy(x).cuda()
+    d_lbs = [dev(b) for b in lbs]
+    batch = fv.Batch([torch.zeros((T, K), device="cuda")] + [d_lbs[b % 3] for b in range(n)])
+    print(f"T={T}", flush=True)
+    fv.decode_batch(dev(la), batch, None, method="vanilla")
+    torch.cuda.synchronize()
+    paths, scores, status = batch.paths.cpu().numpy(), batch.scores.cpu().numpy(), batch.status.cpu().numpy()
+    assert (status == fv.FV_OK).all()
+    assert scores[0] == 0 and (paths[0][:T] == 0).all()
+    for b in range(n):
+        po, so, _ = refs[b % 3]
+        assert scores[1 + b] == so, (b, scores[1 + b], so)
+        np.testing.assert_array_equal(paths[1 + b][:po.shape[0]], po)
