@@ -325,6 +325,15 @@ fv_status fv_profile_engine_ms(float* ms);
  * values return FV_E_INVALID_ARG. */
 fv_status fv_debug_engine_limits(int64_t max_steps, int64_t spin_limit);
 
+/* Test hook for the waits between blocks of the decodes that take whole tasks
+ * (see the decode flags).  Nonzero turns replace, for later decodes issued by
+ * this host thread, the bound on each such wait (by default minutes for a
+ * step's or a publication's, far more for whole passes; looked at every 64
+ * turns).  A wait that reaches it ends, its decode stops normally on every
+ * block and reports FV_E_DEVICE in every status entry.  0 restores the
+ * defaults; negative values return FV_E_INVALID_ARG. */
+fv_status fv_debug_wait_turns(int64_t turns);
+
 /* Measurement hook: while set (steps > 0, host thread-local), persistent
  * engine decodes issued by this thread record, for each of their first
  * `steps` global steps, 16 words in trace[step * 16 ...] (device buffer,

@@ -76,6 +76,7 @@ static thread_local bool g_prof_recorded = false;
 // step and barrier-wait limits for decodes issued by this host thread
 static thread_local int64_t g_dbg_max_steps = 0;
 static thread_local int64_t g_dbg_spin_limit = 0;
+static thread_local int64_t g_dbg_wait_turns = 0;   // fv_debug_wait_turns
 static thread_local unsigned long long* g_dbg_trace = nullptr;
 static thread_local int32_t g_dbg_trace_steps = 0;
 
@@ -835,6 +836,8 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         // beam: exact re-decodes add at most one pass per subtask
         a.max_steps = g_dbg_max_steps ? g_dbg_max_steps : (meth == FV_BEAM ? 16 : 8) * (L.sum_T + L.n_tasks) + 4096;
         a.bounded = bnd.teams || beams[p];
+        a.step_turns = g_dbg_wait_turns ? g_dbg_wait_turns : kStepTurns;
+        a.pass_turns = g_dbg_wait_turns ? g_dbg_wait_turns : kPassTurns;
         if (bnd.teams) {
             a.b_leaf = bnd.leaf;
             a.b_split = bnd.split;
@@ -1006,6 +1009,12 @@ fv_status fv_debug_engine_limits(int64_t max_steps, int64_t spin_limit) {
     if (max_steps < 0 || spin_limit < 0) return fail(FV_E_INVALID_ARG, "limits must be >= 0");
     g_dbg_max_steps = max_steps;
     g_dbg_spin_limit = spin_limit;
+    return FV_OK;
+}
+
+fv_status fv_debug_wait_turns(int64_t turns) {
+    if (turns < 0) return fail(FV_E_INVALID_ARG, "turns must be >= 0");
+    g_dbg_wait_turns = turns;
     return FV_OK;
 }
 

@@ -40,7 +40,6 @@ constexpr int kBThreads = 64 * kBW;
 constexpr int kHash = 2048;           // slots of the sparse step's table
 constexpr int kHashFill = 1536;       // candidates it takes
 constexpr int kInitCap = kHash - kBThreads;   // entries a sparse start holds before it selects
-constexpr int64_t kBeamSpin = 1 << 28;
 
 // A subtask's right child of at least this many positions goes to the queue, a
 // shorter one, like every left child, stays with its block: a publication
@@ -313,18 +312,20 @@ __device__ __forceinline__ void beam_decode(cargs_t& a) {
         __syncthreads();
         if (sp > 0) --sp;   // of the same sequence
         else if (tid == 0) {
+            const int32_t err = ld_c(&st->error);
             const uint32_t h = __hip_atomic_fetch_add(&st->bq_head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int32_t got = h < (uint32_t)n_roots ? 1 : 0;
+            int32_t got = h < (uint32_t)n_roots && !err ? 1 : 0;
             // spawned tasks: wait for the publication of this ticket, or for the
             // end of every task that could still spawn (each is running on some
             // block, so the wait ends)
-            for (int64_t spin = 0; !got && spin < kBeamSpin; ++spin) {
+            for (int64_t turn = 0; !got && !err; ++turn) {
                 const uint32_t live = ld_c(&st->bq_live);
                 if (ld_c(&st->bq_pub) > h) { got = 1; break; }
                 if (live == 0) {
                     got = ld_c(&st->bq_pub) > h ? 1 : 0;
                     break;
                 }
+                if (wait_over(st, turn, a.pass_turns)) break;
                 __builtin_amdgcn_s_sleep(16);
             }
             unsigned long long w0 = 0, w1 = 0;
@@ -735,10 +736,12 @@ __device__ __forceinline__ void beam_decode(cargs_t& a) {
                 __builtin_amdgcn_s_waitcnt(0);
                 if (lane == 0) {
                     // publications follow the reservations' order (the earlier one is
-                    // being written by a running block)
-                    for (int64_t spin = 0; spin < kBeamSpin && ld_c(&st->bq_pub) != pos; ++spin)
+                    // being written by a running block); none after a wait that gave up
+                    bool next = false;
+                    for (int64_t turn = 0; !(next = ld_c(&st->bq_pub) == pos) && !wait_over(st, turn, a.step_turns); ++turn)
                         __builtin_amdgcn_s_sleep(1);
-                    __hip_atomic_fetch_add(&st->bq_pub, (uint32_t)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (next)
+                        __hip_atomic_fetch_add(&st->bq_pub, (uint32_t)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             } else {
                 __builtin_amdgcn_s_waitcnt(0);

@@ -255,20 +255,22 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             unsigned long long w0 = 0, w1 = 0, w2 = 0;
             int32_t got = 0;
             if (member == 0) {
+                const int32_t err = ld_c(&st->error);
                 const uint32_t h =
                     __hip_atomic_fetch_add(&st->bq_head, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                got = h < (uint32_t)n_roots ? 1 : 0;
+                got = h < (uint32_t)n_roots && !err ? 1 : 0;
                 // spawned tasks: wait for the publication of this ticket, or for
                 // the end of every task that could still spawn (each is running
                 // on some team, so the wait ends)
-                if (!got && a.method == FV_FLASH) {
-                    for (int64_t spin = 0; spin < kTeamSpin; ++spin) {
+                if (!got && !err && a.method == FV_FLASH) {
+                    for (int64_t turn = 0;; ++turn) {
                         const uint32_t live = ld_c(&st->bq_live);
                         if (ld_c(&st->bq_pub) > h) { got = 1; break; }
                         if (live == 0) {
                             got = ld_c(&st->bq_pub) > h ? 1 : 0;
                             break;
                         }
+                        if (wait_over(st, turn, a.pass_turns)) break;
                         __builtin_amdgcn_s_sleep(16);
                     }
                 }
@@ -296,8 +298,9 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     st_c(tb.desc, task_no);
                 }
             } else {
-                for (int64_t spin = 0; spin < kTeamSpin; ++spin) {
+                for (int64_t turn = 0;; ++turn) {
                     if (ld_c(tb.desc) == task_no) { got = 1; break; }
+                    if (wait_over(st, turn, a.pass_turns)) break;
                     __builtin_amdgcn_s_sleep(1);
                 }
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -449,7 +452,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             constexpr int CN = NS < 4 ? NS : 4;
             unsigned long long v[CN];
             auto poll = [&](int32_t c) {   // words of states tid + c kTThreads, ...
-                for (int64_t spin = 0; spin < kTeamSpin; ++spin) {
+                for (int64_t turn = 0;; ++turn) {
                     bool bad = false;
 #pragma unroll
                     for (int k = 0; k < CN; ++k) {
@@ -459,8 +462,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     }
 #pragma unroll
                     for (int k = 0; k < CN; ++k) bad = bad || (uint32_t)(v[k] >> 49) != tag;
-                    if (__builtin_amdgcn_ballot_w64(bad) == 0) break;
-                    if (spin == kTeamSpin - 1) st_c(&st->error, 1);
+                    if (__builtin_amdgcn_ballot_w64(bad) == 0 || wait_over(st, turn, a.step_turns)) break;
                 }
                 if (c == 0 && tid == 0) s.sv[7] = (int32_t)(v[0] >> 48) & 1;
             };
@@ -478,10 +480,11 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     for (int32_t k0 = 0; k0 < ngt; k0 += 64) {
                         const bool in = k0 + lane < ngt;
                         unsigned long long q = 0;
-                        for (int64_t spin = 0; spin < kTeamSpin; ++spin) {
+                        for (int64_t turn = 0;; ++turn) {
                             if (in) q = ld_c(tb.g[xp] + k0 + lane);
-                            if (__builtin_amdgcn_ballot_w64(in && (uint32_t)(q >> 48) != tag) == 0) break;
-                            if (spin == kTeamSpin - 1) st_c(&st->error, 1);
+                            if (__builtin_amdgcn_ballot_w64(in && (uint32_t)(q >> 48) != tag) == 0 ||
+                                wait_over(st, turn, a.step_turns))
+                                break;
                         }
                         if (in) mk = max(mk, (uint32_t)q);
                     }
@@ -976,10 +979,8 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 continue;
             }
             for (int32_t k = 1 + tid; k < M; k += kTThreads)
-                for (int64_t spin = 0; spin < kTeamSpin; ++spin) {
-                    if (ld_c(tb.done + k) == task_no) break;
+                for (int64_t turn = 0; ld_c(tb.done + k) != task_no && !wait_over(st, turn, a.step_turns); ++turn)
                     __builtin_amdgcn_s_sleep(1);
-                }
             __syncthreads();
         }
         auto last_x = [&](int32_t j) {
@@ -1105,10 +1106,12 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 __builtin_amdgcn_s_waitcnt(0);
                 if (lane == 0 && cnt > 0) {
                     // publications follow the reservations' order (the earlier one is
-                    // being written by a running block)
-                    for (int64_t spin = 0; spin < kTeamSpin && ld_c(&st->bq_pub) != pos; ++spin)
+                    // being written by a running block); none after a wait that gave up
+                    bool next = false;
+                    for (int64_t turn = 0; !(next = ld_c(&st->bq_pub) == pos) && !wait_over(st, turn, a.step_turns); ++turn)
                         __builtin_amdgcn_s_sleep(1);
-                    __hip_atomic_fetch_add(&st->bq_pub, (uint32_t)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (next)
+                        __hip_atomic_fetch_add(&st->bq_pub, (uint32_t)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
         }

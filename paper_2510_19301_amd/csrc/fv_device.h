@@ -126,6 +126,19 @@ __device__ __forceinline__ float emission(cargs_t& a, const float* lb, int64_t l
     return emission_of(a.emit_kind, a.emit_xy, a.emit_c2, a.emit_c0, lb, ld, t, j);
 }
 
+// Waits for another block (decodes off the lock-step engine) end by count or
+// once the decode has an error, which all of its blocks then see: true on a turn
+// (counted from 0) that is the last one.  A wait that ends so leaves the error
+// set, and the decode reports it whatever the block goes on to do.
+__device__ __forceinline__ bool wait_over(EngineState* st, int64_t turn, int64_t limit) {
+    if ((turn & 63) != 63) return false;
+    if (turn >= limit) {
+        st_c(&st->error, 1);
+        return true;
+    }
+    return uni(ld_c(&st->error)) != 0;
+}
+
 template <int CTRL, int ROWS>
 __device__ __forceinline__ uint32_t dpp_u(uint32_t v) {   // zero where no lane is the source
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int32_t)v, CTRL, ROWS, 0xf, false);

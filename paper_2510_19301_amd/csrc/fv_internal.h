@@ -76,11 +76,17 @@ constexpr int32_t kLeafMaxKp = 2048;   // larger K: no leaves (table too large p
 constexpr int32_t kColMaxKp = 4096;
 
 // Bounded decodes (fv_bound.hip): the largest K, groups of 64 columns a
-// block owns at most, blocks at most (one a CU), and the bound on any wait (each waits for a running block; far above any valid one).
+// block owns at most, blocks at most (one a CU).
 constexpr int32_t kBoundMaxK = 16384;
 constexpr int kTeamGroups = 16;
 constexpr int32_t kTeamBlocks = 256;
-constexpr int64_t kTeamSpin = (int64_t)1 << 28;
+
+// Turns (about a microsecond each) of a wait for another block in decodes off
+// the lock-step engine.  Each waits for a running block: for its next step or
+// publication (at most milliseconds), or for the end of whole passes, which
+// sequences of tens of millions of steps can draw out to minutes.
+constexpr int64_t kStepTurns = (int64_t)1 << 28;
+constexpr int64_t kPassTurns = (int64_t)1 << 36;
 
 // Vanilla and FLASH decodes of a dense model with K <= kSmallK, and FLASH
 // bisections to the paper's minimum with K <= kSmallFlashK, run on one block
@@ -255,6 +261,8 @@ struct EngineArgs {
     double emit_c2, emit_c0;    // log B_t(j) = (float)(c2 * d2 - c0)
     // decodes off the lock-step engine (fv_bound.hip, fv_beam.hip)
     int32_t bounded;            // the decode started there: the engine takes what is left in the queue
+    int64_t step_turns;         // turns of their waits (kStepTurns, kPassTurns)
+    int64_t pass_turns;
     int32_t b_leaf;             // segments of at most this many positions keep backpointers
     int32_t b_split;            // longer ones are split into at most this many
     uint32_t* cmax;             // [K] column maxima of log A as order keys
