@@ -325,7 +325,7 @@ __device__ __forceinline__ void beam_decode(cargs_t& a) {
                     got = ld_c(&st->bq_pub) > h ? 1 : 0;
                     break;
                 }
-                if (wait_over(st, turn, a.pass_turns)) break;
+                if (wait_over(a, turn, true)) break;
                 __builtin_amdgcn_s_sleep(16);
             }
             unsigned long long w0 = 0, w1 = 0;
@@ -738,7 +738,7 @@ __device__ __forceinline__ void beam_decode(cargs_t& a) {
                     // publications follow the reservations' order (the earlier one is
                     // being written by a running block); none after a wait that gave up
                     bool next = false;
-                    for (int64_t turn = 0; !(next = ld_c(&st->bq_pub) == pos) && !wait_over(st, turn, a.step_turns); ++turn)
+                    for (int64_t turn = 0; !(next = ld_c(&st->bq_pub) == pos) && !wait_over(a, turn, false); ++turn)
                         __builtin_amdgcn_s_sleep(1);
                     if (next)
                         __hip_atomic_fetch_add(&st->bq_pub, (uint32_t)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

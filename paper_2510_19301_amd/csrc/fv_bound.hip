@@ -270,7 +270,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                             got = ld_c(&st->bq_pub) > h ? 1 : 0;
                             break;
                         }
-                        if (wait_over(st, turn, a.pass_turns)) break;
+                        if (wait_over(a, turn, true)) break;
                         __builtin_amdgcn_s_sleep(16);
                     }
                 }
@@ -300,7 +300,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             } else {
                 for (int64_t turn = 0;; ++turn) {
                     if (ld_c(tb.desc) == task_no) { got = 1; break; }
-                    if (wait_over(st, turn, a.pass_turns)) break;
+                    if (wait_over(a, turn, true)) break;
                     __builtin_amdgcn_s_sleep(1);
                 }
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
@@ -462,7 +462,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     }
 #pragma unroll
                     for (int k = 0; k < CN; ++k) bad = bad || (uint32_t)(v[k] >> 49) != tag;
-                    if (__builtin_amdgcn_ballot_w64(bad) == 0 || wait_over(st, turn, a.step_turns)) break;
+                    if (__builtin_amdgcn_ballot_w64(bad) == 0 || wait_over(a, turn, false)) break;
                 }
                 if (c == 0 && tid == 0) s.sv[7] = (int32_t)(v[0] >> 48) & 1;
             };
@@ -483,7 +483,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                         for (int64_t turn = 0;; ++turn) {
                             if (in) q = ld_c(tb.g[xp] + k0 + lane);
                             if (__builtin_amdgcn_ballot_w64(in && (uint32_t)(q >> 48) != tag) == 0 ||
-                                wait_over(st, turn, a.step_turns))
+                                wait_over(a, turn, false))
                                 break;
                         }
                         if (in) mk = max(mk, (uint32_t)q);
@@ -979,7 +979,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 continue;
             }
             for (int32_t k = 1 + tid; k < M; k += kTThreads)
-                for (int64_t turn = 0; ld_c(tb.done + k) != task_no && !wait_over(st, turn, a.step_turns); ++turn)
+                for (int64_t turn = 0; ld_c(tb.done + k) != task_no && !wait_over(a, turn, false); ++turn)
                     __builtin_amdgcn_s_sleep(1);
             __syncthreads();
         }
@@ -1108,7 +1108,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     // publications follow the reservations' order (the earlier one is
                     // being written by a running block); none after a wait that gave up
                     bool next = false;
-                    for (int64_t turn = 0; !(next = ld_c(&st->bq_pub) == pos) && !wait_over(st, turn, a.step_turns); ++turn)
+                    for (int64_t turn = 0; !(next = ld_c(&st->bq_pub) == pos) && !wait_over(a, turn, false); ++turn)
                         __builtin_amdgcn_s_sleep(1);
                     if (next)
                         __hip_atomic_fetch_add(&st->bq_pub, (uint32_t)cnt, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -130,13 +130,18 @@ __device__ __forceinline__ float emission(cargs_t& a, const float* lb, int64_t l
 // once the decode has an error, which all of its blocks then see: true on a turn
 // (counted from 0) that is the last one.  A wait that ends so leaves the error
 // set, and the decode reports it whatever the block goes on to do.
-__device__ __forceinline__ bool wait_over(EngineState* st, int64_t turn, int64_t limit) {
+// (The arguments are read on the turns that look at them: kept in scalar
+// registers across the steps, others would be spilled.)
+__device__ __forceinline__ bool wait_over(cargs_t& args, int64_t turn, bool pass) {
     if ((turn & 63) != 63) return false;
-    if (turn >= limit) {
-        st_c(&st->error, 1);
+    uint64_t p = reinterpret_cast<uint64_t>(&args);
+    asm volatile("" : "+s"(p));
+    cargs_t& a = *reinterpret_cast<cargs_t*>(p);
+    if (turn >= (pass ? a.pass_turns : a.step_turns)) {
+        st_c(&a.st->error, 1);
         return true;
     }
-    return uni(ld_c(&st->error)) != 0;
+    return uni(ld_c(&a.st->error)) != 0;
 }
 
 template <int CTRL, int ROWS>
