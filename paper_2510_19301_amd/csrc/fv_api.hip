@@ -496,7 +496,8 @@ bool use_wide_rows(uint32_t flags, int32_t K, int32_t n_seqs, bool sparse) {
 // and how many teams run them.
 struct BoundPlan {
     int32_t teams = 0;   // 0: the lock-step engine decodes this model
-    int32_t leaf = 0, split = 0, rows = 0;
+    int32_t leaf = 0, split = 0;
+    bool leaves = false;   // passes that the bound does not prune are left to the engine
     int64_t scratch = 0;
 };
 
@@ -529,9 +530,7 @@ BoundPlan plan_bounded(uint32_t flags, bool per_seq, int32_t method, const fv_tr
         }
         b.split = b.leaf / 4;
     }
-    // the lists hold every state up to K = 1024; beyond, a root that mostly
-    // leaves them goes to the engine, whose step costs the same whatever the scores
-    if (A->K > 1024) b.rows = 1;
+    b.leaves = A->K > 1024 || team_kernel(A->K, L.team) == 2;
     return b;
 }
 
@@ -707,7 +706,7 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
             !g_dbg_trace && std::min(B, A->K) <= kBeamBlockB && (A->kind == FV_CSR || A->K <= kBeamBlockK))
             beams[p] = di.cus * std::max(1, di.beam_blocks_per_cu[A->kind == FV_CSR ? 1 : 0]);
         bounds[p] = plan_bounded(flags, per_seq, bp.method[p], &models[bp.model[p]], bp.L[p], di);
-        engine = engine || bounds[p].teams == 0 || bounds[p].rows > 0;
+        engine = engine || bounds[p].teams == 0 || bounds[p].leaves;
     }
     for (size_t p = 0; p < bp.L.size(); ++p) {
         const DenseLayout& L = bp.L[p];
@@ -927,7 +926,7 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         const void* const fn = team[team_kernel(K, bp.L[p].team)];
         if (bp.L[p].team > 1) HIP_TRY(hipLaunchCooperativeKernel(fn, grid, dim3(kTeamBlock), targs, 0, stream));
         else HIP_TRY(hipLaunchKernel(fn, grid, dim3(K <= 256 ? kBlock : kTeamBlock), targs, 0, stream));
-        if (bounds[p].rows > 0 && args[p].At)
+        if (bounds[p].leaves && args[p].At)
             hipLaunchKernelGGL(fv_transpose_dense_kernel, dim3(args[p].Kp / 64, args[p].Kp / 64), dim3(kBlock), 0,
                                stream, args[p].Acol, args[p].Kp, const_cast<float*>(args[p].At), &args[p].st->q_tail0);
     }

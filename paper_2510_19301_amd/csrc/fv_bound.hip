@@ -63,6 +63,16 @@ constexpr int kTiers = 3;
 // a new one (swept: 1.0 / 1.6 / 1.1 / 0.3 takes 2% longer, h at 0.9 needs the
 // second reading in 78% instead of 35% of the steps and takes 20% longer)
 constexpr float kNear = 0.9f, kFar = 1.4f, kHalf = 1.15f, kEma = 0.2f;
+// Where the bound does not prune, the engine's step, which costs the same
+// whatever the scores, is the shorter one, and a pass is left to it: a vanilla
+// pass or a root that reads more than 3 K / 4 rows a step (FILTER; 3 K are free;
+// all K rows: 37 us a step, the engine's for 256 sequences of K = 1024 24 to 30),
+// any pass that reads more than K / 32 rows a step outside the lists (FAR; K / 4
+// are free, 16 K to a segment, whose root kept within them; such a row takes
+// 0.1 to 0.2 us, an engine's step 30 to 200 us from K = 4096 to 16384).
+// Up to K = 512, and for a team of blocks, reading every row is no slower than
+// the engine, or little.
+constexpr int32_t kQuitCap = 1 << 30;   // counted up to here
 constexpr int32_t kBoundRetry = 77;   // sequence status: left to the lock-step engine
 constexpr int kRowCap = 128;          // rows of a wave's lists (FILTER)
 
@@ -177,7 +187,6 @@ struct TeamBuf {
     unsigned long long* g[2];
     unsigned long long* desc;
     unsigned long long* done;
-    unsigned long long* beyond;   // scans of the task that left the lists
 };
 __device__ __forceinline__ TeamBuf team_buf(char* base, int32_t Kp, int32_t M) {
     unsigned long long* w = reinterpret_cast<unsigned long long*>(base);
@@ -190,7 +199,6 @@ __device__ __forceinline__ TeamBuf team_buf(char* base, int32_t Kp, int32_t M) {
     b.g[1] = b.g[0] + ng;
     b.desc = b.g[1] + ng;
     b.done = b.desc + 16;
-    b.beyond = b.desc + 8;
     return b;
 }
 // score | tracked division state | stop mark | step tag (15 bits)
@@ -210,6 +218,10 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
     constexpr int UL = UN / 4;               // 16 lanes across 64 columns: 4 entries side by side
     // long rows: the groups' maxima are polled first, the words then read once
     constexpr bool GATE = TEAM && KC > 4096;
+    // passes that the bound does not prune are left to the engine: ones that read
+    // nearly all listed states (FILTER), or many on no list for want of room (FAR)
+    constexpr bool FAR = TEAM && LC < KC;
+    constexpr bool QUIT = FAR || FILTER;
     __shared__ __align__(16) TeamLds<KC, LC, NB, TEAM, FILTER> s;
     const int32_t tid = threadIdx.x, lane = tid & 63, wv = uni(tid >> 6);
     const int32_t K = a.K, Kp = a.Kp, M = a.b_team;
@@ -287,7 +299,6 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                         w2 = (unsigned long long)__float_as_uint(al) | ((unsigned long long)(qn | qp << 16) << 32);
                     }
                 }
-                st_c(tb.beyond, 0ull);
                 if (M > 1) {
                     st_c(tb.desc + 1, w0);
                     st_c(tb.desc + 2, w1);
@@ -318,6 +329,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             s.sv[4] = (int32_t)(w1 >> 32);
             s.sv[5] = (int32_t)w2;
             s.sv[6] = (int32_t)(w2 >> 32);
+            s.sv[7] = 0;
         }
         __syncthreads();
         if (!s.sv[0]) break;
@@ -401,7 +413,10 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
         int32_t d_next = 0;
         int32_t e_next = mode == BM_DIV && w > 1 ? div_end(0) : -1, e_prev = -1;
         const int32_t e_first = e_next;
-        uint32_t give_up = 0;      // the first group's mark: this task is left to the engine
+        uint32_t give_up = 0;      // this group's mark: the pass is left to the engine
+        // rows of log A that the group read: listed ones (FILTER), in excess of what
+        // a step may take, and ones on no list (FAR), which one wave reads by itself
+        int32_t listed = 0, far = 0;
         auto publish = [&](int32_t t, float xn, int32_t mid) {
             const uint32_t tag = (epoch + (uint32_t)(t - m)) & kTagBits;
             const int32_t p = (int32_t)(epoch + (uint32_t)(t - m)) & 1;
@@ -414,7 +429,9 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             if constexpr (!TEAM || GATE) {
                 const uint32_t mk = wave_max(score_key(xn));
                 if (lane == 0) {
-                    if constexpr (TEAM) st_c(tb.g[p] + gb + g, (unsigned long long)mk | ((unsigned long long)tag << 48));
+                    if constexpr (TEAM)
+                        st_c(tb.g[p] + gb + g, (unsigned long long)mk | ((unsigned long long)give_up << 32) |
+                                                   ((unsigned long long)tag << 48));
                     else atomicMax(&s.rmax[p], mk);
                 }
             }
@@ -464,7 +481,12 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     for (int k = 0; k < CN; ++k) bad = bad || (uint32_t)(v[k] >> 49) != tag;
                     if (__builtin_amdgcn_ballot_w64(bad) == 0 || wait_over(a, turn, false)) break;
                 }
-                if (c == 0 && tid == 0) s.sv[7] = (int32_t)(v[0] >> 48) & 1;
+                if constexpr (FAR && !GATE) {
+                    uint32_t stop = 0;
+#pragma unroll
+                    for (int k = 0; k < CN; ++k) stop |= (uint32_t)(v[k] >> 48) & 1;
+                    if (stop) s.sv[7] = 1;
+                }
             };
             if constexpr (TEAM && !GATE) {
                 poll(0);
@@ -476,7 +498,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             }
             if constexpr (GATE) {
                 if (wv == 0) {   // one wave polls the groups' maxima: more would slow what they wait for
-                    uint32_t mk = 0;
+                    uint32_t mk = 0, stop = 0;
                     for (int32_t k0 = 0; k0 < ngt; k0 += 64) {
                         const bool in = k0 + lane < ngt;
                         unsigned long long q = 0;
@@ -487,9 +509,11 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                                 break;
                         }
                         if (in) mk = max(mk, (uint32_t)q);
+                        if (in) stop |= (uint32_t)(q >> 32) & 1;
                     }
                     mk = wave_max(mk);
                     if (lane == 0) s.rmax[xp] = mk;
+                    if (stop) s.sv[7] = 1;
                 }
             }
             __syncthreads();
@@ -569,10 +593,10 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 for (int32_t k = tid; k < TC; k += kTThreads) s.part[k] = 0;
             if (tid == 0) s.need[par ^ 1] = 0;   // every wave is past its reads of the step before
             if (tid == 1) s.rmax[xp ^ 1] = 0;
-            const bool quit = TEAM && LC < KC && s.sv[7] != 0;
+            const bool quit = QUIT && s.sv[7] != 0;
             __syncthreads();
-            if (quit) {   // its scans mostly leave the lists: the bound does not prune this
-                retry = true;                   // input, and the engine's step costs the same whatever the scores
+            if (quit) {   // the bound does not prune these scores, and the engine's step costs the
+                retry = true;                   // same whatever they are
                 made = step + 1;                // (every block stops here: the mark came with this row)
                 break;
             }
@@ -711,12 +735,6 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 const float nd = D - (b - s.cm[jl]);   // NaN where nothing is needed
                 const uint32_t mx = wave_max(nd > 0.0f && nd < INFINITY ? __float_as_uint(nd) : 0u);
                 if (lane == 0) atomicMax(&s.need[par ^ 1], mx);
-                if (TEAM && LC < KC) {
-                    if (out && lane == 0)
-                        __hip_atomic_fetch_add(tb.beyond, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (member == 0 && g == 0 && (step & 15) == 15)
-                        give_up = ld_c(tb.beyond) > (unsigned long long)ngt * (unsigned long long)(8 + step / 8) ? 1u : 0u;
-                }
             };
             if constexpr (FILTER) {
                 if (active) {
@@ -739,6 +757,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                         BoundEnt e0[U], e1[U];
                         vec_t v0[U], v1[U];
                         const int32_t most = max(n0, n1);
+                        listed += most;
                         // both lists to a multiple of 16 at the longer one's end: rows that cannot win
                         for (int32_t e = min(n0, n1) + (lane & 15); e < most + 16; e += 16) {
                             if (e >= n0) s.rows[wv][0][e] = BoundEnt{flip, -INFINITY};
@@ -852,6 +871,10 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     if (step == 0) F1 = fmaxf(F1 + 0.5f * (u - F1), 1e-4f);
                     else F = fmaxf(F + kEma * (u - F), 1e-4f);
                     finish(top, thr, 0, more, 0.0f, 0);
+                    if (kind != KIND_SUB && (step & 15) == 15) {
+                        listed = max(listed - 12 * K, -kQuitCap);
+                        if (listed > 3 * K && lane == 0) s.sv[7] = 1;
+                    }
                 }
             } else {
                 double best[4] = {none, none, none, none};
@@ -913,7 +936,13 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     const bool out = !stop && outside;
                     float fo = -INFINITY;
                     int32_t qo = 0;
-                    if (out) {
+                    // (of a first list without room for them, more than LC)
+                    auto beyond_reason = [&](int32_t rows) {
+                        const int64_t most = K / 4 + (int64_t)step * (K / 32) + (kind == KIND_SUB ? 16 * K : 0);
+                        return FAR && t < n && far + rows > min(most, (int64_t)kQuitCap);
+                    };
+                    bool drop = out && lists == 0 && beyond_reason(LC);
+                    if (out && !drop) {
                         // none that scores below thr can win (checked, not derived: the
                         // subtraction is rounded)
                         const float bs = __int_as_float(__double2hiint(top)), cm = s.cm[jl];
@@ -928,10 +957,15 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
 #pragma unroll
                             for (int u = 0; u < 4; ++u)
                                 xo[u] = score_at(min(c0 + u * 64 + lane, K - 1));
+                            if constexpr (FAR) {
+                                drop = beyond_reason(0);   // with the rows read so far
+                                if (drop) break;
+                            }
 #pragma unroll
                             for (int u = 0; u < 4; ++u) {
                                 const bool in = c0 + u * 64 + lane < K && xo[u] >= thr && xo[u] < top_of;
                                 uint64_t mask = __builtin_amdgcn_ballot_w64(in);
+                                if constexpr (FAR) far = min(far + (int32_t)__popcll(mask), kQuitCap);
                                 while (mask) {   // four rows in flight
                                     int32_t r[4];
                                     float v[4];
@@ -951,7 +985,12 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                         }
                         top = max64(top, __hiloint2double(__float_as_int(fo), qo ^ flip));
                     }
-                    finish(top, 0.0f, k, out, fo, qo);
+                    if (drop) {   // no one reads this row's scores
+                        give_up = 1;
+                        publish(t, -INFINITY, 0);
+                    } else {
+                        finish(top, 0.0f, k, out, fo, qo);
+                    }
                 }
             }
             if (t == e_next) {
