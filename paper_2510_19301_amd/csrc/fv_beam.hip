@@ -48,6 +48,7 @@ constexpr int kInitCap = kHash - kBThreads;   // entries a sparse start holds be
 // queued, 14.4 with these).
 constexpr int kBeamShare = 12;
 constexpr int kBeamStack = 32;
+constexpr int kBeamRank = 256;        // members of a bin that are ranked one by one, at most
 
 struct BeamTask {
     int32_t m, n, q_prev, q_n;
@@ -74,6 +75,7 @@ struct BeamBlk {
     int32_t sv_[8];
     BeamTask stack[kBeamStack];       // this block's subtasks
     unsigned long long key;
+    unsigned long long clo, chi;      // range of the bin's members
 };
 
 // Order of scores as unsigned numbers (-0 and +0 equal); 0 for none.
@@ -112,6 +114,98 @@ __device__ __forceinline__ void beam_out_range(cargs_t& a, int32_t s, int32_t& e
     x1 = x1 < x0 ? x0 : (x1 > a.nnz ? a.nnz : x1);
     e0 = (int32_t)x0;
     e1 = (int32_t)x1;
+}
+
+// The bin that holds the b-th of n entries counted in hist (those counted
+// nowhere belong to the last bin); the entries in front of it and in it.  The
+// same in every lane.
+__device__ __forceinline__ int32_t beam_bin(const uint32_t* hist, int32_t n, int32_t b, int32_t& before, int32_t& in) {
+    const int32_t lane = threadIdx.x & 63;
+    uint4 c = *reinterpret_cast<const uint4*>(&hist[4 * lane]);
+    int32_t own = (int32_t)(c.x + c.y + c.z + c.w);
+    int32_t upto = wave_scan(own);
+    const int32_t others = n - __builtin_amdgcn_readlane(upto, 63);
+    if (lane == 63) {
+        c.w += (uint32_t)others;
+        own += others;
+        upto = n;
+    }
+    const uint64_t reach = __builtin_amdgcn_ballot_w64(upto >= b);
+    const int32_t src = (int32_t)__builtin_ctzll(reach);   // n >= b: some lane reaches b
+    int32_t kb = 4 * src;
+    before = __builtin_amdgcn_readlane(upto - own, src);
+    in = __builtin_amdgcn_readlane((int32_t)c.x, src);
+    const int32_t c1 = __builtin_amdgcn_readlane((int32_t)c.y, src), c2 = __builtin_amdgcn_readlane((int32_t)c.z, src),
+                  c3 = __builtin_amdgcn_readlane((int32_t)c.w, src);
+    if (before + in < b) { before += in; in = c1; ++kb; }
+    if (before + in < b) { before += in; in = c2; ++kb; }
+    if (before + in < b) { before += in; in = c3; ++kb; }
+    return kb;
+}
+
+// Many entries in the bin that holds the B-th (equal scores, or a depth unlike
+// the last beam's): 256 bins over the bits of (score, state) in which they
+// differ, until few are left.  1024 states' ranks inside one bin take 100 us, such
+// a pass 2.  (Not inlined: the step's loads lose registers to it, 2% of the time
+// of 64 sequences of K = 1024, B = 64.)
+struct BeamCut {
+    int32_t in, take;   // entries in the bin, and how many of them are kept
+    int32_t mask;       // of this thread's: kept (bits 0, 1), in the bin (bits 2, 3)
+};
+__device__ __noinline__ BeamCut beam_narrow(BeamBlk& s, int32_t par, BeamCut c, unsigned long long w0,
+                                            unsigned long long w1) {
+    const int32_t tid = threadIdx.x, lane = tid & 63;
+    unsigned long long w[2] = {w0, w1};   // score and state; 0: not in the bin
+    int32_t kept = 0;
+    while (c.in > kBeamRank) {
+        __syncthreads();
+        if (tid < 256) s.hist[par][tid] = 0;
+        if (tid == 0) {
+            s.ncrit = 0;
+            s.clo = ~0ull;
+            s.chi = 0;
+        }
+        __syncthreads();
+        unsigned long long hi = max(w[0], w[1]);
+        unsigned long long lo = min(w[0] ? w[0] : ~0ull, w[1] ? w[1] : ~0ull);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            lo = min(lo, (unsigned long long)__shfl_xor(lo, off, 64));
+            hi = max(hi, (unsigned long long)__shfl_xor(hi, off, 64));
+        }
+        if (lane == 0 && hi != 0) {
+            atomicMin(&s.clo, lo);
+            atomicMax(&s.chi, hi);
+        }
+        __syncthreads();
+        hi = s.chi;
+        const int32_t shift = max(0, 56 - __clzll((long long)(hi - s.clo)));   // (states differ)
+        int32_t bin[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            bin[k] = (int32_t)((hi - w[k]) >> shift);
+            if (w[k]) atomicAdd(&s.hist[par][bin[k]], 1u);
+        }
+        __syncthreads();
+        int32_t before, in;
+        const int32_t kb = beam_bin(s.hist[par], c.in, c.take, before, in);
+        c.take -= before;
+        c.in = in;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            if (!w[k]) continue;
+            if (bin[k] < kb || (bin[k] == kb && in == c.take)) kept |= 1 << k;
+            if (bin[k] != kb || in == c.take) w[k] = 0;
+            if (w[k] && in <= kBeamRank) {
+                const int32_t p = atomicAdd(&s.ncrit, 1);
+                s.ckey[p] = (uint32_t)(w[k] >> 32);
+                s.cst[p] = 0x7fffffff - (int32_t)(uint32_t)w[k];
+            }
+        }
+        if (in == c.take) break;
+    }
+    c.mask = kept | (w[0] ? 4 : 0) | (w[1] ? 8 : 0);
+    return c;
 }
 
 // The entries to keep of a block's v[0 .. NV) (-inf: none) with states st:
@@ -164,25 +258,8 @@ __device__ __forceinline__ void beam_keep(BeamBlk& s, int32_t B, uint32_t step, 
     __syncthreads();
     if (n <= B) return;
     // the bin that holds the B-th score (each wave finds it)
-    uint4 c = *reinterpret_cast<const uint4*>(&s.hist[par][4 * lane]);
-    int32_t own = (int32_t)(c.x + c.y + c.z + c.w);
-    int32_t upto = wave_scan(own);
-    const int32_t others = n - __builtin_amdgcn_readlane(upto, 63);
-    if (lane == 63) {
-        c.w = (uint32_t)others;
-        own += others;
-        upto = n;
-    }
-    const uint64_t reach = __builtin_amdgcn_ballot_w64(upto >= B);
-    const int32_t src = (int32_t)__builtin_ctzll(reach);   // n > B entries are counted: some lane reaches B
-    int32_t before = __builtin_amdgcn_readlane(upto - own, src), kb = 4 * src;
-    int32_t cb = __builtin_amdgcn_readlane((int32_t)c.x, src);
-    const int32_t c1 = __builtin_amdgcn_readlane((int32_t)c.y, src), c2 = __builtin_amdgcn_readlane((int32_t)c.z, src),
-                  c3 = __builtin_amdgcn_readlane((int32_t)c.w, src);
-    if (before + cb < B) { before += cb; cb = c1; ++kb; }
-    if (before + cb < B) { before += cb; cb = c2; ++kb; }
-    if (before + cb < B) { before += cb; cb = c3; ++kb; }
-    const int32_t rem = B - before;
+    int32_t before, cb, kb = beam_bin(s.hist[par], n, B, before, cb);
+    int32_t rem = B - before;
     bool crit[NV];
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
@@ -197,6 +274,22 @@ __device__ __forceinline__ void beam_keep(BeamBlk& s, int32_t B, uint32_t step, 
     // bins of about 1/80 of this beam's depth next
     inv = fminf(fmaxf(80.0f * inv / (float)(kb + 1), 1e-30f), 1e30f);
     if (cb == rem) return;
+    if (cb > kBeamRank) {
+        unsigned long long w[2];
+        static_assert(NV == 2, "entries per thread");
+#pragma unroll
+        for (int k = 0; k < NV; ++k)
+            w[k] = crit[k] ? (unsigned long long)beam_key(v[k]) << 32 | (uint32_t)(0x7fffffff - st[k]) : 0ull;
+        const BeamCut c = beam_narrow(s, par, BeamCut{cb, rem, 0}, w[0], w[1]);
+        cb = uni(c.in);
+        rem = uni(c.take);
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            keep[k] = keep[k] || (c.mask >> k & 1);
+            crit[k] = c.mask >> (2 + k) & 1;
+        }
+        if (cb == rem) return;
+    }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
