@@ -21,8 +21,8 @@
 //           the bin that holds the B-th.
 // Arithmetic, ties and the subtask structure are the engine's.  A subtask whose
 // beam lost its end state needs the exact re-decode, and a step with more
-// candidates than the table holds needs the engine's sort: such sequences are
-// left to the engine from their roots.
+// candidates than the table holds needs the engine's sort: such tasks, and what
+// they spawn, are left to the engine, which runs after this kernel.
 //
 // Measured against the engine: 64 sequences, K = 1024, T ~ U[200, 2000], B = 64,
 // P = 16: 91.4 -> 14.5 ms; 64 trajectories on 99,856 states, T ~ U[200, 2000],
@@ -34,7 +34,6 @@
 
 namespace fv {
 
-constexpr int32_t kBeamRetry = 77;    // sequence status: left to the lock-step engine
 constexpr int kBW = 16;               // waves of a block
 constexpr int kBThreads = 64 * kBW;
 constexpr int kHash = 2048;           // slots of the sparse step's table
@@ -429,7 +428,6 @@ __device__ __forceinline__ void beam_decode(cargs_t& a) {
                 w1 = ld_c(p + 1);
                 const SeqInfo& sq = a.seqs[(int32_t)w0];
                 const int32_t tm = (int32_t)w1, tn = (int32_t)(w1 >> 32);
-                s.sv_[5] = ld_c(&sq.status);
                 tk.m = tm;
                 tk.n = tn;
                 if ((int32_t)(w0 >> 32) == KIND_BSUB) {
@@ -450,9 +448,8 @@ __device__ __forceinline__ void beam_decode(cargs_t& a) {
         const int32_t T = sq.T, pp = sq.pp, tmid = (m + n) >> 1;
         const int32_t q_prev = uni(s.stack[sp].q_prev), q_n = root ? 0 : uni(s.stack[sp].q_n);
         const float alpha = s.stack[sp].alpha;
-        const int32_t status = uni(s.sv_[5]);
-        bool retry = !root && status != kBeamRetry && (q_n < 0 || q_n >= K || (m > 0 && (q_prev < 0 || q_prev >= K)));
-        bool skip = status == kBeamRetry || status < 0;
+        bool retry = !root && (q_n < 0 || q_n >= K || (m > 0 && (q_prev < 0 || q_prev >= K)));
+        bool lost = false;        // retry, since the beam has no edge to the end state
         int32_t nb = 0, q = 0;    // the beam's entries and parity
         gfloat_t* const lb = as_global(sq.log_b);
         const int64_t ld = sq.ld;
@@ -514,7 +511,7 @@ __device__ __forceinline__ void beam_decode(cargs_t& a) {
             nb = beam_lay_out<NV>(s, B, q ^ 1, v, sx, an, keep);
             q ^= 1;
         };
-        if (!skip && !retry) {
+        if (!retry) {
             // ---- start: pi + log B_0, or the anchored boundary state's row
             if constexpr (SPARSE) {
                 if (m == 0) {
@@ -702,7 +699,7 @@ __device__ __forceinline__ void beam_decode(cargs_t& a) {
         // ---- end of the task: the block's stores complete (the chain reads them)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (!skip && !retry && !root) {
+        if (!retry && !root) {
             // only the known end state is scored
             if (tid == 0) s.key = 0;
             __syncthreads();
@@ -721,19 +718,29 @@ __device__ __forceinline__ void beam_decode(cargs_t& a) {
             }
             if (key) atomicMax(&s.key, key);
             __syncthreads();
-            if (s.key == 0) retry = true;   // the beam lost q*_n
+            retry = lost = s.key == 0;   // the beam lost q*_n
         }
         __syncthreads();
         // a subtask's children: the right one on the queue if it is long
-        const bool right = !skip && !retry && !root && n - m > 2, share = right && n - tmid >= kBeamShare;
+        const bool right = !retry && !root && n - m > 2, share = right && n - tmid >= kBeamShare;
         const int32_t base = sp;
-        if (skip || retry) sp = 0;
-        else if (!root) sp += (n - m >= 2 ? 1 : 0) + (right && !share ? 1 : 0);
+        if (!retry && !root) sp += (n - m >= 2 ? 1 : 0) + (right && !share ? 1 : 0);
         if (wv == 0) {
             int32_t cnt = 0;
-            if (skip) {
-            } else if (retry) {
-                if (lane == 0) st_c(&sq.status, kBeamRetry);
+            if (retry) {
+                // the engine's tasks: the second half of the queue (this kernel's take
+                // at most the first)
+                if (lane == 0) {
+                    if (lost) st_c(&sq.status, (int32_t)FV_W_BEAM_FALLBACK);
+                    const int64_t p = a.q_cap / 2 + __hip_atomic_fetch_add(&st->bq_left, 1u, __ATOMIC_RELAXED,
+                                                                           __HIP_MEMORY_SCOPE_AGENT);
+                    const int32_t kind = root ? KIND_BROOT : (lost ? KIND_FSUB : KIND_BSUB);
+                    if (p < a.q_cap) {
+                        uint64_t* qe = reinterpret_cast<uint64_t*>(a.queue + p);
+                        st_c(qe, (uint64_t)(uint32_t)seq | ((uint64_t)(uint32_t)kind << 32));
+                        st_c(qe + 1, (uint64_t)(uint32_t)m | ((uint64_t)(uint32_t)n << 32));
+                    }
+                }
             } else if (!root) {
                 if (lane == 0) {
                     const int32_t w = clampi((int32_t)(0xFFFFFFFFu - (uint32_t)(s.key & 0xFFFFFFFFull)), nb);
@@ -747,7 +754,6 @@ __device__ __forceinline__ void beam_decode(cargs_t& a) {
                     if (right && !share) s.stack[base] = BeamTask{tmid + 1, n, qmid, q_n, am};
                     // the next of this block's subtasks is of this sequence's kind
                     s.sv_[2] = KIND_BSUB;
-                    s.sv_[5] = ld_c(&sq.status);
                 }
                 cnt = share ? 1 : 0;
             } else if (nb == 0) {
@@ -848,31 +854,23 @@ __device__ __forceinline__ void beam_decode(cargs_t& a) {
                 if (tid == 0) s.ncand = 0;
             }
     }
-    // ---- the last block leaves the sequences it could not decode to the engine
+    // ---- the last block hands the engine its tasks
     __syncthreads();
     if (tid == 0) {
         __builtin_amdgcn_s_waitcnt(0);
         s.sv_[0] = __hip_atomic_fetch_add(&st->bq_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == gridDim.x;
     }
     __syncthreads();
-    if (!s.sv_[0] || wv != 0) return;
-    int32_t left = 0;
-    for (int32_t k0 = 0; k0 < n_roots; k0 += 64) {
-        const int32_t k = k0 + lane;
-        Task tk{};
-        bool again = false;
-        if (k < n_roots) {
-            tk = a.queue[k];
-            again = ld_c(&a.seqs[tk.seq].status) == kBeamRetry;
-        }
-        const uint64_t mask = __builtin_amdgcn_ballot_w64(again);
-        if (again) {
-            a.queue[left + __popcll(mask & ((1ull << lane) - 1))] = tk;
-            st_c(&a.seqs[tk.seq].status, (int32_t)FV_OK);
-        }
-        left += __popcll(mask);
+    if (!s.sv_[0]) return;
+    const int64_t half = a.q_cap / 2;
+    const int32_t left = (int32_t)min((int64_t)ld_c(&st->bq_left), a.q_cap - half);
+    for (int32_t k = tid; k < left; k += kBThreads) {
+        const unsigned long long* p = reinterpret_cast<const unsigned long long*>(a.queue + half + k);
+        uint64_t* qe = reinterpret_cast<uint64_t*>(a.queue + k);
+        st_c(qe, (uint64_t)ld_c(p));
+        st_c(qe + 1, (uint64_t)ld_c(p + 1));
     }
-    if (lane == 0) st->q_tail0 = left;
+    if (tid == 0) st->q_tail0 = left;
 }
 
 extern "C" __global__ __launch_bounds__(kBThreads, 4) void fv_beam_dense_kernel(const EngineArgs* __restrict__ table) {

@@ -171,9 +171,10 @@ struct EngineState {
     int32_t claim[2][kXcd][kLine];     // [parity][xcd] next unclaimed work unit of a step
     int32_t wclaim[2][kLine];          // [parity] next unclaimed wide item of a step
     // bounded decode (fv_bound.hip): task tickets taken, queue entries
-    // reserved and published, tasks not finished, blocks that ended
+    // reserved and published, tasks not finished, blocks that ended, tasks left
+    // to the engine (fv_beam.hip)
     uint32_t bq_head, bpad0[kLine - 1];
-    uint32_t bq_res, bq_pub, bq_live, bq_done, bpad1[kLine - 4];
+    uint32_t bq_res, bq_pub, bq_live, bq_done, bq_left, bpad1[kLine - 5];
     // a step's row counts of each XCD, tagged with the epoch of the barrier
     // that publishes them (see pack_counts), so that a block waiting at that
     // barrier receives them with its release flag
