@@ -25,7 +25,9 @@ extern "C" __global__ void fv_small_flash256_kernel(const EngineArgs* __restrict
 extern "C" __global__ void fv_bound256_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_bound512_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_bound1k_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_bound1k_short_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_team1k_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_team1k_short_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_team4k_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_team16k_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_beam_dense_kernel(const EngineArgs* __restrict__ table);
@@ -148,6 +150,7 @@ struct DenseLayout {
     int64_t div_off = 0;         // their offset in a slot, in floats
     int32_t leaf_len = 0;        // the longest leaf that can occur (table rows per slot)
     int64_t leaf_off = 0;        // its offset in a slot, in floats
+    int32_t max_T = 0;           // longest sequence
     int32_t max_seg = 0;         // longest first-level FLASH segment, in positions
     int64_t n_segs = 0;          // first-level FLASH segments of at least two positions
     int32_t team = 0, teams = 0; // bounded decodes: blocks of a team, and teams (0: not bounded)
@@ -238,6 +241,7 @@ fv_status plan_dense(int32_t method, const fv_trans* A, const int32_t* T_host, i
         if (T < 0) return fail(FV_E_INVALID_ARG, "sequence %d has negative length %d", b, T);
         L.sum_T += T;
         max_T = std::max<int64_t>(max_T, T);
+        L.max_T = std::max(L.max_T, T);
         if (T == 0) continue;
         ++nonempty;
         if (method == FV_VANILLA) {
@@ -511,6 +515,9 @@ BoundPlan plan_bounded(uint32_t flags, bool per_seq, int32_t method, const fv_tr
     if (!L.teams || (flags & FV_FLAG_ENGINE)) return b;
     if (!per_seq && ((flags & ~(uint32_t)FV_FLAG_VALIDATE) || g_dbg_max_steps || g_dbg_spin_limit || g_dbg_trace))
         return b;
+    // short sequences of states that may not all be on the lists: a pass that is
+    // given up takes 0.3 ms, the engine's for T = 16 0.5 (K = 3000) to 3.3 ms (16384)
+    if (A->K > kBoundListK && L.max_T <= kShortT) return b;
     // the blocks of the teams wait for each other: all of them are resident
     const int32_t resident = di.cus * di.team_blocks_per_cu[team_kernel(A->K, L.team)];
     if (resident < L.team) return b;
@@ -703,7 +710,7 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
     for (size_t p = 0; p < bp.L.size() && !small; ++p) {
         const fv_trans* A = &models[bp.model[p]];
         if (bp.method[p] == FV_BEAM && !(flags & ~(uint32_t)FV_FLAG_VALIDATE) && !g_dbg_max_steps && !g_dbg_spin_limit &&
-            !g_dbg_trace && std::min(B, A->K) <= kBeamBlockB && (A->kind == FV_CSR || A->K <= kBeamBlockK))
+            !g_dbg_trace && std::min(B, A->K) <= kBeamBlockB && (A->kind == FV_CSR ? A->nnz * std::min(B, A->K) <= (int64_t)kBeamCands * A->K : A->K <= kBeamBlockK))
             beams[p] = di.cus * std::max(1, di.beam_blocks_per_cu[A->kind == FV_CSR ? 1 : 0]);
         bounds[p] = plan_bounded(flags, per_seq, bp.method[p], &models[bp.model[p]], bp.L[p], di);
         engine = engine || bounds[p].teams == 0 || bounds[p].leaves;
@@ -923,7 +930,9 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
                                      reinterpret_cast<const void*>(fv_team1k_kernel),
                                      reinterpret_cast<const void*>(fv_team4k_kernel),
                                      reinterpret_cast<const void*>(fv_team16k_kernel)};
-        const void* const fn = team[team_kernel(K, bp.L[p].team)];
+        const void* fn = team[team_kernel(K, bp.L[p].team)];
+        if (bp.L[p].max_T <= kShortT && fn == team[2]) fn = reinterpret_cast<const void*>(fv_bound1k_short_kernel);
+        if (bp.L[p].max_T <= kShortT && fn == team[3]) fn = reinterpret_cast<const void*>(fv_team1k_short_kernel);
         if (bp.L[p].team > 1) HIP_TRY(hipLaunchCooperativeKernel(fn, grid, dim3(kTeamBlock), targs, 0, stream));
         else HIP_TRY(hipLaunchKernel(fn, grid, dim3(K <= 256 ? kBlock : kTeamBlock), targs, 0, stream));
         if (bounds[p].leaves && args[p].At)

@@ -37,7 +37,7 @@ namespace fv {
 constexpr int kBW = 16;               // waves of a block
 constexpr int kBThreads = 64 * kBW;
 constexpr int kHash = 2048;           // slots of the sparse step's table
-constexpr int kHashFill = 1536;       // candidates it takes
+constexpr int kHashFill = kBeamCands; // candidates it takes
 constexpr int kInitCap = kHash - kBThreads;   // entries a sparse start holds before it selects
 
 // A subtask's right child of at least this many positions goes to the queue, a

@@ -83,11 +83,17 @@ constexpr int kRowCap = 128;          // rows of a wave's lists (FILTER)
 // Equal scores are decided by the low word: the smaller one is the larger
 // number for negative scores, the larger one for positive scores, so the
 // state is stored as itself while scores are negative and complemented while
-// they are positive (`finish` handles columns of the other sign, and zeros).
+// they are positive.  A step that may have candidates of both signs, or zeros,
+// decides it for each (`mixed`: two instructions more, and one that makes -0
+// +0); `finish` handles columns of a sign that was not expected.
 struct BoundEnt {
     int32_t lo;
     float v;
 };
+// a state, in a mixed step: as itself for a negative score, complemented for others
+__device__ __forceinline__ int32_t by_sign(float score, int32_t i) { return i ^ ~(__float_as_int(score) >> 31); }
+struct Mixed { static constexpr bool on = true; };
+struct OneSign { static constexpr bool on = false; };
 
 // KC: the largest K, LC: states a list holds, NB: steps whose emission rows
 // are fetched, and backpointer rows stored, at once.  (Memory operations of a
@@ -109,6 +115,7 @@ struct TeamLds {
     unsigned long long part[FILTER ? 1 : TC];   // order keys of partial maxima
     uint32_t rb[FILTER ? 16 * KC : 1];   // [groups, Kp] row bounds of both halves
     float cm[TC];                  // column maxima; NaN where no scan is ever needed
+    float cm_lo, cm_hi;            // the smallest and the largest of them
     uint16_t pb[2][NB * TC];       // backpointer rows: being made, being stored
     uint16_t anc[TEAM ? 1 : 2][KC];    // tracked division state of every state
     float x[TEAM ? 1 : 2][TEAM ? 1 : KC];   // a single block's scores, by step parity
@@ -209,8 +216,8 @@ __device__ __forceinline__ unsigned long long team_word(float v, uint32_t mid, u
 
 enum : int32_t { BM_VANILLA = 0, BM_DIV = 1, BM_LEAF = 2 };
 
-// W: waves of a block.
-template <int KC, int LC, int NB, bool TEAM, int W, bool FILTER>
+// W: waves of a block.  MIX: steps that may have results of both signs scan so.
+template <int KC, int LC, int NB, bool TEAM, int W, bool FILTER, bool MIX>
 __device__ __forceinline__ void team_decode(cargs_t& a) {
     constexpr int kTThreads = 64 * W;
     constexpr int TC = TeamLds<KC, LC, NB, TEAM, FILTER>::TC;
@@ -255,6 +262,28 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
     }
     if constexpr (FILTER)
         for (int32_t k = tid; k < ngl * Kp; k += kTThreads) s.rb[k] = a.rowb[k];
+    float cm_lo = 0.0f, cm_hi = 0.0f;
+    if constexpr (MIX) {
+        __syncthreads();
+        if (wv == 0) {
+            uint32_t lo = 0, hi = 0;
+            for (int32_t k = lane; k < cn; k += 64) {
+                const float c = s.cm[k];
+                if (!(c == c)) continue;
+                lo = max(lo, score_key(-c));
+                hi = max(hi, score_key(c));
+            }
+            lo = wave_max(lo);
+            hi = wave_max(hi);
+            if (lane == 0) {
+                s.cm_lo = -score_of_key(lo);
+                s.cm_hi = score_of_key(hi);
+            }
+        }
+        __syncthreads();
+        cm_lo = __int_as_float(uni(__float_as_int(s.cm_lo)));
+        cm_hi = __int_as_float(uni(__float_as_int(s.cm_hi)));
+    }
     const double none = __hiloint2double((int32_t)0xff800000u, 0);
     float G = 8.0f, G1 = 16.0f;   // distance below the maximum that the scans are expected to need
     float F = 8.0f, F1 = 16.0f;   // and (FILTER) those of the lane's half group
@@ -525,7 +554,15 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 else G = fmaxf(G + 0.25f * (u - G), 1e-4f);
             }
             const bool neg = D < 0.0f;
-            const int32_t flip = neg ? 0 : -1;
+            // a step that may have results of both signs: none is above D + cm_hi, most are
+            // above D - 4 G + cm_lo.  (All ones or 0, in scalar arithmetic: branches
+            // here and at the result cost such kernels 4%.)
+            int32_t mixm = 0;
+            if constexpr (MIX)
+                mixm = uni(-(((int32_t)neg & (int32_t)(D + cm_hi >= 0.0f)) |
+                             ((int32_t)!neg & (int32_t)(D + cm_lo <= 4.0f * (step == 0 ? G1 : G)))));
+            const bool mixed = mixm != 0, plain = MIX ? neg || mixed : neg;
+            const int32_t flip = plain ? 0 : -1;   // stored states
             // ---- the lists
             // scores from which a state is on the first, second, third list: the
             // first holds what all groups are expected to need, or, where each
@@ -614,8 +651,8 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             // above every score outside the first n lists
             auto below = [&](int32_t n) { return n == 0 ? INFINITY : (n == 1 ? h0 : (n == 2 ? h1 : h2)); };
             // ---- scan of the groups' columns
-            const int32_t mul = neg ? pitch : -pitch;   // row offset of a list entry from its stored form
-            const int32_t add0 = cb * 4 - (neg ? 0 : pitch);
+            const int32_t mul = plain ? pitch : -pitch;   // row offset of a list entry from its stored form
+            const int32_t add0 = cb * 4 - (plain ? 0 : pitch);
             // entries of a list of cnt from `at` on (the last one repeated past its end)
             auto load = [&](auto& en, auto& av, const BoundEnt* list, int32_t at, int32_t cnt, int32_t add) {
                 constexpr int N = sizeof(en) / sizeof(en[0]);
@@ -626,13 +663,24 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     av[u] = *reinterpret_cast<gvec_t*>(A + (uint32_t)(__mul24(en[u].lo, mul) + add));
                 __builtin_amdgcn_sched_barrier(0);   // every load is issued before the next wait
             };
-            auto scan = [&](double (&best)[4], const auto& en, const auto& av) {
+            auto scan = [&](auto mx, double (&best)[4], const auto& en, const auto& av) {
                 constexpr int N = sizeof(en) / sizeof(en[0]);
 #pragma unroll
                 for (int u = 0; u < N; ++u)
 #pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        best[c] = max64(best[c], __hiloint2double(__float_as_int(en[u].v + av[u][c]), en[u].lo));
+                    for (int c = 0; c < 4; ++c) {
+                        float x = en[u].v + av[u][c];
+                        if (mx.on) x += 0.0f;   // -0: +0
+                        best[c] = max64(best[c], __hiloint2double(__float_as_int(x), mx.on ? by_sign(x, en[u].lo) : en[u].lo));
+                    }
+            };
+            // the pattern of a candidate x of state i, and the state of a pattern
+            auto pattern = [&](float x, int32_t i) {
+                if (mixed) x += 0.0f;
+                return __hiloint2double(__float_as_int(x), i ^ flip ^ (mixm & ~(__float_as_int(x) >> 31)));
+            };
+            auto state_of = [&](double b) {
+                return __double2loint(b) ^ flip ^ (mixm & ~(__double2hiint(b) >> 31));
             };
             auto score_at = [&](int32_t i) {
                 if constexpr (TEAM) return __uint_as_float((uint32_t)ld_c(tb.x[xp] + i));
@@ -682,7 +730,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 float f;
                 int32_t q;
                 scan_states(thr, top_of, f, q);
-                return max64(top, __hiloint2double(__float_as_int(f), q ^ flip));
+                return max64(top, pattern(f, q));
             };
             // the result of this wave's group: the sign check, the score, the state
             // and the division state.  Scanned were (FILTER) the states from thr on
@@ -690,13 +738,26 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
             // them, whose best is fo of qo.
             auto finish = [&](double top, float thr, int32_t done, bool out, float fo, int32_t qo) {
                 // scores of the other sign, or zeros, where the low word does not
-                // order equal candidates: compare by value and state
+                // order equal candidates: compare by value and state.  (A mixed
+                // step's is in order; a zero gets its own sign back.)
                 const float b0 = __int_as_float(__double2hiint(top));
-                const bool odd = neg ? b0 >= 0.0f : (b0 <= 0.0f && b0 > -INFINITY);
+                bool odd;
+                if constexpr (MIX) {
+                    const int32_t negm = uni(-(int32_t)neg);
+                    const float odd_lo = __int_as_float(flip & __float_as_int(-FLT_MAX));
+                    const float odd_hi = __int_as_float(negm & ~mixm & __float_as_int(INFINITY));
+                    odd = b0 >= odd_lo && b0 <= odd_hi;
+                } else {
+                    odd = neg ? b0 >= 0.0f : (b0 <= 0.0f && b0 > -INFINITY);
+                }
                 if (__builtin_amdgcn_ballot_w64(odd)) {
                     float f = -INFINITY;
                     int32_t q = 0;
-                    if constexpr (FILTER) {
+                    if (mixed) {
+                        f = b0;
+                        q = state_of(top);
+                        if (odd) f = score_at(q) + as_global(a.Acol)[(uint32_t)q * (uint32_t)Kp + cb + jl];
+                    } else if constexpr (FILTER) {
                         scan_states(thr, INFINITY, f, q);
                     } else {
                         gfloat_t* const ak = as_global(a.Acol) + cb + jl;
@@ -715,10 +776,10 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                         }
                         if (out) take1(f, q, fo, qo);
                     }
-                    top = __hiloint2double(__float_as_int(f), q ^ flip);
+                    top = __hiloint2double(__float_as_int(f), q ^ flip ^ (mixm & ~(__float_as_int(f) >> 31)));
                 }
                 const float b = __int_as_float(__double2hiint(top));
-                const int32_t arg = b > -INFINITY ? __double2loint(top) ^ flip : 0;
+                const int32_t arg = b > -INFINITY ? state_of(top) : 0;
                 const float xn = jl < cn ? b + s.eb[half][row * TC + jl] : -INFINITY;
                 int32_t mid = 0;
                 if (mode == BM_DIV) {
@@ -763,17 +824,27 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                             if (e >= n0) s.rows[wv][0][e] = BoundEnt{flip, -INFINITY};
                             if (e >= n1) s.rows[wv][1][e] = BoundEnt{flip, -INFINITY};
                         }
+                        if (mixed) {
+#pragma unroll 1
+                            for (int32_t e = 0; e < most; e += inc) {
+                                fetch_rows(e0, v0, 0, e);
+                                fetch_rows(e1, v1, 1, e);
+                                scan(Mixed{}, b0, e0, v0);
+                                scan(Mixed{}, b1, e1, v1);
+                            }
+                            return;
+                        }
                         fetch_rows(e0, v0, 0, 0);
                         fetch_rows(e1, v1, 1, 0);
 #pragma unroll 1
                         for (int32_t e = inc; e < most; e += inc) {
-                            scan(b0, e0, v0);
+                            scan(OneSign{}, b0, e0, v0);
                             fetch_rows(e0, v0, 0, e);
-                            scan(b1, e1, v1);
+                            scan(OneSign{}, b1, e1, v1);
                             fetch_rows(e1, v1, 1, e);
                         }
-                        scan(b0, e0, v0);
-                        scan(b1, e1, v1);
+                        scan(OneSign{}, b0, e0, v0);
+                        scan(OneSign{}, b1, e1, v1);
                     };
                     const uint32_t* const rb = s.rb + g * Kp;
                     // listed states with bounds from the lane's lo up to (not including) its hi
@@ -881,9 +952,8 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                 const int32_t add = (g * 64 + lc4) * 4 + add0;
                 // the waves of a group share its first lists (the first alone when
                 // the group is one wave's) without a look at the bound
-                int32_t k = 0;
-                if (active) {
-                    for (; k < min(wpg > 1 ? 2 : 1, lists); ++k) {
+                if (active && !mixed) {
+                    for (int32_t k = 0; k < min(wpg > 1 ? 2 : 1, lists); ++k) {
                         const BoundEnt* const list = s.list[k];
                         const int32_t cnt = uni(s.cnt[par][k]), inc = wpg * UN;
                         BoundEnt e0[UL], e1[UL];
@@ -893,20 +963,31 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                         load(e0, v0, list, e, cnt, add);
                         for (; e + 2 * inc < cnt; e += 2 * inc) {
                             load(e1, v1, list, e + inc, cnt, add);
-                            scan(best, e0, v0);
+                            scan(OneSign{}, best, e0, v0);
                             load(e0, v0, list, e + 2 * inc, cnt, add);
-                            scan(best, e1, v1);
+                            scan(OneSign{}, best, e1, v1);
                         }
                         if (e + inc < cnt) {
                             load(e1, v1, list, e + inc, cnt, add);
-                            scan(best, e0, v0);
-                            scan(best, e1, v1);
+                            scan(OneSign{}, best, e0, v0);
+                            scan(OneSign{}, best, e1, v1);
                         } else {
-                            scan(best, e0, v0);
+                            scan(OneSign{}, best, e0, v0);
+                        }
+                    }
+                } else if (active) {
+                    for (int32_t k = 0; k < min(wpg > 1 ? 2 : 1, lists); ++k) {
+                        const int32_t cnt = uni(s.cnt[par][k]), inc = 2 * wpg * UN;
+#pragma unroll 1
+                        for (int32_t e = 2 * sub * UN; e < cnt; e += inc) {
+                            BoundEnt e0[2 * UL];
+                            vec_t v0[2 * UL];
+                            load(e0, v0, s.list[k], e, cnt, add);
+                            scan(Mixed{}, best, e0, v0);
                         }
                     }
                 }
-                k = min(wpg > 1 ? 2 : 1, lists);
+                int32_t k = min(wpg > 1 ? 2 : 1, lists);
                 double top = merge_group(best);
                 if (wpg > 1) {
                     if (active) atomicMax(&s.part[jl], pattern_key(top));
@@ -926,7 +1007,8 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                             BoundEnt e0[2 * UL];
                             vec_t v0[2 * UL];
                             load(e0, v0, s.list[k], e, cnt, add);
-                            scan(more, e0, v0);
+                            if (mixed) scan(Mixed{}, more, e0, v0);
+                            else scan(OneSign{}, more, e0, v0);
                         }
                         ++k;
                         top = max64(top, merge_group(more));
@@ -983,7 +1065,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                                 }
                             }
                         }
-                        top = max64(top, __hiloint2double(__float_as_int(fo), qo ^ flip));
+                        top = max64(top, pattern(fo, qo));
                     }
                     if (drop) {   // no one reads this row's scores
                         give_up = 1;
@@ -1186,22 +1268,26 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
 }
 
 // One block per task for K <= 256, 512 and 1024, teams for K <= 1024, 4096
-// and 16384.  A block takes a CU's 16 wavefronts (two blocks of 8 for one task
+// and 16384; two for short sequences (kShortT), whose scores may be of both
+// signs: in the others of their kind that costs the common step 3 to 7% (registers),
+// in the rest nothing.  A block takes a CU's 16 wavefronts (two blocks of 8 for one task
 // each: 158 instead of 112 ms for 256 sequences of K = 1024, FLASH P = 64, whose
 // roots then leave half of them idle); up to K = 256, with a wave for each
 // group and rows enough for one or two units, three blocks of 4 share a CU:
 // 512 sequences of K = 256, T ~ U[32, 512], FLASH P = 16 and the score's gradients
 // take 2.6 ms (8 waves each: 2.5, 16: 3.9; 64 sequences of K = 200: 1.5, 1.7, 1.7).
-#define FV_TEAM(NAME, KC, LC, NB, TEAM, W, FILTER)                                                              \
-    extern "C" __global__ __launch_bounds__(64 * W, W == 4 ? 3 : 4) void NAME(const EngineArgs* __restrict__ table) {           \
-        team_decode<KC, LC, NB, TEAM, W, FILTER>(*reinterpret_cast<cargs_t*>(reinterpret_cast<uint64_t>(table))); \
+#define FV_TEAM(NAME, KC, LC, NB, TEAM, W, FILTER, MIX)                                                         \
+    extern "C" __global__ __launch_bounds__(64 * W, W == 4 ? 3 : 4) void NAME(const EngineArgs* __restrict__ table) {                \
+        team_decode<KC, LC, NB, TEAM, W, FILTER, MIX>(*reinterpret_cast<cargs_t*>(reinterpret_cast<uint64_t>(table))); \
     }
-FV_TEAM(fv_bound256_kernel, 256, 256, 8, false, 4, false)
-FV_TEAM(fv_bound512_kernel, 1024, 1024, 4, false, 16, false)
-FV_TEAM(fv_bound1k_kernel, 1024, 1024, 2, false, 16, true)
-FV_TEAM(fv_team1k_kernel, 1024, 1024, 4, true, 16, false)
-FV_TEAM(fv_team4k_kernel, 4096, 2048, 4, true, 16, false)
-FV_TEAM(fv_team16k_kernel, 16384, 2048, 2, true, 16, false)
+FV_TEAM(fv_bound256_kernel, 256, 256, 8, false, 4, false, true)
+FV_TEAM(fv_bound512_kernel, 1024, 1024, 4, false, 16, false, true)
+FV_TEAM(fv_bound1k_kernel, 1024, 1024, 2, false, 16, true, false)
+FV_TEAM(fv_bound1k_short_kernel, 1024, 1024, 2, false, 16, true, true)
+FV_TEAM(fv_team1k_kernel, 1024, 1024, 4, true, 16, false, false)
+FV_TEAM(fv_team1k_short_kernel, 1024, 1024, 4, true, 16, false, true)
+FV_TEAM(fv_team4k_kernel, 4096, kBoundListK, 4, true, 16, false, true)
+FV_TEAM(fv_team16k_kernel, 16384, kBoundListK, 2, true, 16, false, true)
 #undef FV_TEAM
 
 // Row bounds: rowb[g][i] (two float16) >= max over the 32 columns of either half
