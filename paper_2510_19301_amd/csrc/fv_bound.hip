@@ -67,11 +67,12 @@ constexpr float kNear = 0.9f, kFar = 1.4f, kHalf = 1.15f, kEma = 0.2f;
 // whatever the scores, is the shorter one, and a pass is left to it: a vanilla
 // pass or a root that reads more than 3 K / 4 rows a step (FILTER; 3 K are free;
 // all K rows: 37 us a step, the engine's for 256 sequences of K = 1024 24 to 30),
-// any pass that reads more than K / 32 rows a step outside the lists (FAR; K / 4
-// are free, 16 K to a segment, whose root kept within them; such a row takes
-// 0.1 to 0.2 us, an engine's step 30 to 200 us from K = 4096 to 16384).
-// Up to K = 512, and for a team of blocks, reading every row is no slower than
-// the engine, or little.
+// any pass that reads more than K / 32 rows a step outside the first lists (FAR;
+// K / 8 are free, 16 K to a segment, whose root kept within them; such a row takes
+// 0.1 to 0.2 us, on the third list a quarter of that, an engine's step 30 to 200 us
+// from K = 4096 to 16384).  Up to K = 512, and for a team of blocks whose lists
+// have room for all states, reading every row is no slower than the engine, or
+// little.
 constexpr int32_t kQuitCap = 1 << 30;   // counted up to here
 constexpr int32_t kBoundRetry = 77;   // sequence status: left to the lock-step engine
 constexpr int kRowCap = 128;          // rows of a wave's lists (FILTER)
@@ -1010,6 +1011,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                             if (mixed) scan(Mixed{}, more, e0, v0);
                             else scan(OneSign{}, more, e0, v0);
                         }
+                        if (FAR && K > LC) far = min(far + cnt / 4, kQuitCap);   // (by one wave, 16 rows in flight, not 4)
                         ++k;
                         top = max64(top, merge_group(more));
                         stop = closed();
@@ -1020,10 +1022,10 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
                     int32_t qo = 0;
                     // (of a first list without room for them, more than LC)
                     auto beyond_reason = [&](int32_t rows) {
-                        const int64_t most = K / 4 + (int64_t)step * (K / 32) + (kind == KIND_SUB ? 16 * K : 0);
+                        const int64_t most = K / (K > LC ? 8 : 4) + (int64_t)step * (K / 32) + (kind == KIND_SUB ? 16 * K : 0);
                         return FAR && t < n && far + rows > min(most, (int64_t)kQuitCap);
                     };
-                    bool drop = out && lists == 0 && beyond_reason(LC);
+                    bool drop = beyond_reason(out && lists == 0 ? LC : 0);
                     if (out && !drop) {
                         // none that scores below thr can win (checked, not derived: the
                         // subtraction is rounded)

@@ -76,3 +76,23 @@ def test_some_sequences_left_to_the_engine(K, n, method, P):
         out.append((batch.paths.clone(), batch.scores.clone(), batch.status.clone()))
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("method", ["vanilla", "flash"])
+def test_time_of_long_lists(method):
+    """A wide reach: most states are listed, and each step's third list is read by one wave."""
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a GPU")
+    import paper_2510_19301_amd as fv
+    K, T = 3000, 100
+    g = torch.Generator(device="cuda").manual_seed(K)
+    la = torch.log_softmax(4 * torch.randn((K, K), generator=g, device="cuda"), 1)
+    batch = fv.Batch([2 * torch.randn((T, K), generator=g, device="cuda")])
+    ms, out = {}, {}
+    for engine in (True, False):
+        ws = fv.decode_batch(la, batch, None, method=method, P=4, engine=engine)
+        ms[engine] = _ms(lambda: fv.decode_batch(la, batch, None, method=method, P=4, ws=ws, engine=engine))
+        out[engine] = (batch.paths.clone(), batch.scores.clone(), batch.status.clone())
+    for a, b in zip(out[True], out[False]):
+        assert torch.equal(a, b)
+    assert ms[False] < 1.35 * ms[True], ms
