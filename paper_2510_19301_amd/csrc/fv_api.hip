@@ -153,6 +153,7 @@ struct DenseLayout {
     int32_t max_T = 0;           // longest sequence
     int32_t max_seg = 0;         // longest first-level FLASH segment, in positions
     int64_t n_segs = 0;          // first-level FLASH segments of at least two positions
+    int64_t roots = 0;           // sequences that are not empty
     int32_t team = 0, teams = 0; // bounded decodes: blocks of a team, and teams (0: not bounded)
     int64_t xch_bytes = 0;       // a team's exchange buffer
     Region cmax, rowb, xch;      // column maxima, row bounds and exchange buffers of bounded decodes
@@ -244,6 +245,7 @@ fv_status plan_dense(int32_t method, const fv_trans* A, const int32_t* T_host, i
         L.max_T = std::max(L.max_T, T);
         if (T == 0) continue;
         ++nonempty;
+        ++L.roots;
         if (method == FV_VANILLA) {
             L.sum_psi += (int64_t)T * K;
             L.n_tasks += 1;
@@ -496,6 +498,14 @@ bool use_wide_rows(uint32_t flags, int32_t K, int32_t n_seqs, bool sparse) {
     return K >= 4096 || (K >= 1024 && n_seqs <= 4);
 }
 
+// Tenths of a microsecond that a bounded FLASH decode's tasks take to go through
+// their queue: 0.9 us a root's publication, 0.2 us a segment.  For many short
+// sequences that is most of the time, and other ways take less: 256 sequences,
+// P = 16, K = 256: T = 32 bounded 966 us, one block per sequence 408; T = 64 1190
+// and 804; T = 128 no difference.  K = 512, P = 4, the engine: T = 8 508 and 369,
+// T = 16 585 and 564.
+int64_t queue_time(const DenseLayout& L) { return 9 * L.roots + 2 * L.n_segs; }
+
 // Bounded decodes (fv_bound.hip) of one model: how its FLASH passes are cut
 // and how many teams run them.
 struct BoundPlan {
@@ -518,6 +528,8 @@ BoundPlan plan_bounded(uint32_t flags, bool per_seq, int32_t method, const fv_tr
     // short sequences of states that may not all be on the lists: a pass that is
     // given up takes 0.3 ms, the engine's for T = 16 0.5 (K = 3000) to 3.3 ms (16384)
     if (A->K > kBoundListK && L.max_T <= kShortT) return b;
+    // (an engine's step is taken as 30 us, its start as 150)
+    if (method == FV_FLASH && A->K > kBoundSmallK && queue_time(L) > 10 * (150 + 30 * (int64_t)L.max_T)) return b;
     // the blocks of the teams wait for each other: all of them are resident
     const int32_t resident = di.cus * di.team_blocks_per_cu[team_kernel(A->K, L.team)];
     if (resident < L.team) return b;
@@ -694,7 +706,8 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
     // 2.0 against 2.6), beyond it more (K = 130, T = 1000, vanilla: 6.0 against
     // 2.5 ms; 512 sequences of K = 256, FLASH with gradients: 12.7 against 2.6).
     // Bisections to the paper's minimum stay here up to K = 256: bounded FLASH
-    // passes end in leaves.
+    // passes end in leaves.  So do many short sequences (a step is taken as 9 us
+    // more than a bounded one's, and a CU as one sequence's).
     const int32_t small_k = flags & (FV_FLAG_RELATIVE_INIT | FV_FLAG_NO_LEAVES) ? kSmallFlashK : kSmallK;
     // Where every model is dense with K <= kBoundSmallK, the others' flags and
     // hooks choose nothing: relative starts and full bisections are all `small`.
@@ -702,8 +715,11 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
     for (size_t p = 0; p < bp.L.size(); ++p) {
         const int32_t K_ = bp.L[p].K;
         per_seq = per_seq && models[bp.model[p]].kind == FV_DENSE && bp.method[p] != FV_BEAM && K_ <= kBoundSmallK;
+        const DenseLayout& L = bp.L[p];
+        const bool queued = queue_time(L) > 90 * (int64_t)L.max_T * std::max<int64_t>(1, (L.roots + di.cus - 1) / di.cus);
         small = small && per_seq &&
-                ((bp.method[p] == FV_VANILLA && K_ <= kSmallK) || (bp.method[p] == FV_FLASH && K_ <= small_k));
+                ((bp.method[p] == FV_VANILLA && K_ <= kSmallK) ||
+                 (bp.method[p] == FV_FLASH && (K_ <= small_k || (K_ <= kSmallFlashK && queued))));
     }
     bool engine = false;   // the lock-step engine is launched
     std::vector<int32_t> beams(bp.L.size(), 0);   // blocks of a beam decode off the engine
