@@ -25,6 +25,8 @@ extern "C" __global__ void fv_small_flash256_kernel(const EngineArgs* __restrict
 extern "C" __global__ void fv_bound256_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_bound512_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_bound1k_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_bound256_short_kernel(const EngineArgs* __restrict__ table);
+extern "C" __global__ void fv_bound512_short_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_bound1k_short_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_team1k_kernel(const EngineArgs* __restrict__ table);
 extern "C" __global__ void fv_team1k_short_kernel(const EngineArgs* __restrict__ table);
@@ -940,15 +942,18 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
         const EngineArgs* ta = table_dev + p;
         void* targs[] = {&ta};
         const dim3 grid(bounds[p].teams * bp.L[p].team);
-        const void* const team[6] = {reinterpret_cast<const void*>(fv_bound256_kernel),
-                                     reinterpret_cast<const void*>(fv_bound512_kernel),
-                                     reinterpret_cast<const void*>(fv_bound1k_kernel),
-                                     reinterpret_cast<const void*>(fv_team1k_kernel),
-                                     reinterpret_cast<const void*>(fv_team4k_kernel),
-                                     reinterpret_cast<const void*>(fv_team16k_kernel)};
-        const void* fn = team[team_kernel(K, bp.L[p].team)];
-        if (bp.L[p].max_T <= kShortT && fn == team[2]) fn = reinterpret_cast<const void*>(fv_bound1k_short_kernel);
-        if (bp.L[p].max_T <= kShortT && fn == team[3]) fn = reinterpret_cast<const void*>(fv_team1k_short_kernel);
+        const void* const team[10] = {reinterpret_cast<const void*>(fv_bound256_kernel),
+                                      reinterpret_cast<const void*>(fv_bound512_kernel),
+                                      reinterpret_cast<const void*>(fv_bound1k_kernel),
+                                      reinterpret_cast<const void*>(fv_team1k_kernel),
+                                      reinterpret_cast<const void*>(fv_team4k_kernel),
+                                      reinterpret_cast<const void*>(fv_team16k_kernel),
+                                      reinterpret_cast<const void*>(fv_bound256_short_kernel),
+                                      reinterpret_cast<const void*>(fv_bound512_short_kernel),
+                                      reinterpret_cast<const void*>(fv_bound1k_short_kernel),
+                                      reinterpret_cast<const void*>(fv_team1k_short_kernel)};
+        const int kn = team_kernel(K, bp.L[p].team);
+        const void* const fn = team[kn < 4 && bp.L[p].max_T <= kShortT ? 6 + kn : kn];
         if (bp.L[p].team > 1) HIP_TRY(hipLaunchCooperativeKernel(fn, grid, dim3(kTeamBlock), targs, 0, stream));
         else HIP_TRY(hipLaunchKernel(fn, grid, dim3(K <= 256 ? kBlock : kTeamBlock), targs, 0, stream));
         if (bounds[p].leaves && args[p].At)

@@ -1270,9 +1270,11 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
 }
 
 // One block per task for K <= 256, 512 and 1024, teams for K <= 1024, 4096
-// and 16384; two for short sequences (kShortT), whose scores may be of both
-// signs: in the others of their kind that costs the common step 3 to 7% (registers),
-// in the rest nothing.  A block takes a CU's 16 wavefronts (two blocks of 8 for one task
+// and 16384.  Those up to K = 1024 come with MIX for short sequences (kShortT),
+// which costs the common step 3 to 7% (registers), and without for others; above,
+// where one wave's second scan of a step is many times the step, all have it
+// (K = 1243, 93 sequences, FLASH: 27.4 ms without, 28.5 with; K = 4096, T = 100 and
+// scores from above zero: 3.8 and 3.4).  A block takes a CU's 16 wavefronts (two blocks of 8 for one task
 // each: 158 instead of 112 ms for 256 sequences of K = 1024, FLASH P = 64, whose
 // roots then leave half of them idle); up to K = 256, with a wave for each
 // group and rows enough for one or two units, three blocks of 4 share a CU:
@@ -1282,8 +1284,10 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
     extern "C" __global__ __launch_bounds__(64 * W, W == 4 ? 3 : 4) void NAME(const EngineArgs* __restrict__ table) {                \
         team_decode<KC, LC, NB, TEAM, W, FILTER, MIX>(*reinterpret_cast<cargs_t*>(reinterpret_cast<uint64_t>(table))); \
     }
-FV_TEAM(fv_bound256_kernel, 256, 256, 8, false, 4, false, true)
-FV_TEAM(fv_bound512_kernel, 1024, 1024, 4, false, 16, false, true)
+FV_TEAM(fv_bound256_kernel, 256, 256, 8, false, 4, false, false)
+FV_TEAM(fv_bound256_short_kernel, 256, 256, 8, false, 4, false, true)
+FV_TEAM(fv_bound512_kernel, 1024, 1024, 4, false, 16, false, false)
+FV_TEAM(fv_bound512_short_kernel, 1024, 1024, 4, false, 16, false, true)
 FV_TEAM(fv_bound1k_kernel, 1024, 1024, 2, false, 16, true, false)
 FV_TEAM(fv_bound1k_short_kernel, 1024, 1024, 2, false, 16, true, true)
 FV_TEAM(fv_team1k_kernel, 1024, 1024, 4, true, 16, false, false)
