@@ -61,9 +61,10 @@ typedef enum {
 
 enum { FV_DENSE = 0, FV_CSR = 1 };
 
-/* Decode flags (bit set).  Without flags (FV_FLAG_VALIDATE aside) dense
- * vanilla and FLASH decodes up to K = 16384, and beams up to B = 256 on CSR
- * models and dense ones up to K = 2048, run on blocks that take whole tasks;
+/* Decode flags (bit set).  Without flags (FV_FLAG_VALIDATE aside) most dense
+ * vanilla and FLASH decodes up to K = 16384, and beams up to B = 256 on most
+ * CSR models and dense ones up to K = 2048, run on blocks that take whole
+ * tasks, and the persistent engine decodes what those leave and all others;
  * the flags below that choose among the persistent engine's ways mean the
  * engine.  Placement of the engine's rows in flight: by default the
  * library keeps each row on one XCD and tiles rows onto lanes (many rows,

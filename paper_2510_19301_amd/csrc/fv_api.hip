@@ -118,7 +118,7 @@ fv_status fv_set_error(fv_status s, const char* fmt, ...) {
 // symbol): the device address comes from hipGetSymbolAddress, once per
 // device, and is kept in g_scratch_ptr.
 // Beyond FV_NOALLOC_SCRATCH_BYTES it has room for what a bounded decode adds
-// to the lock-step engine's regions (at most 0.4 MB for one sequence), so that
+// to the lock-step engine's regions (at most 0.6 MB for one sequence), so that
 // the sizes the entry point takes are the engine's.
 constexpr size_t kNoallocExtra = 1 << 20;
 static __device__ __align__(256) unsigned char scratch[FV_NOALLOC_SCRATCH_BYTES + kNoallocExtra];
@@ -953,7 +953,7 @@ fv_status run_batch(int32_t method, const fv_trans* models, const float* const* 
                                       reinterpret_cast<const void*>(fv_bound1k_short_kernel),
                                       reinterpret_cast<const void*>(fv_team1k_short_kernel)};
         const int kn = team_kernel(K, bp.L[p].team);
-        const void* const fn = team[kn < 4 && bp.L[p].max_T <= kShortT ? 6 + kn : kn];
+        const void* const fn = team[kn < 4 && bp.L[p].max_T <= kMixT ? 6 + kn : kn];
         if (bp.L[p].team > 1) HIP_TRY(hipLaunchCooperativeKernel(fn, grid, dim3(kTeamBlock), targs, 0, stream));
         else HIP_TRY(hipLaunchKernel(fn, grid, dim3(K <= 256 ? kBlock : kTeamBlock), targs, 0, stream));
         if (bounds[p].leaves && args[p].At)

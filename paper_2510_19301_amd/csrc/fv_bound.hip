@@ -1270,7 +1270,7 @@ __device__ __forceinline__ void team_decode(cargs_t& a) {
 }
 
 // One block per task for K <= 256, 512 and 1024, teams for K <= 1024, 4096
-// and 16384.  Those up to K = 1024 come with MIX for short sequences (kShortT),
+// and 16384.  Those up to K = 1024 come with MIX for short sequences (kMixT),
 // which costs the common step 3 to 7% (registers), and without for others; above,
 // where one wave's second scan of a step is many times the step, all have it
 // (K = 1243, 93 sequences, FLASH: 27.4 ms without, 28.5 with; K = 4096, T = 100 and

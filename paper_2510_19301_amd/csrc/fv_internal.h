@@ -95,12 +95,13 @@ constexpr int64_t kPassTurns = (int64_t)1 << 36;
 constexpr int32_t kSmallK = 128;
 constexpr int32_t kSmallFlashK = 256;
 constexpr int32_t kBoundSmallK = 256;
-// Short sequences.  Up to K = 1024 they take the bounded kernels for scores of
-// both signs (MIX in fv_bound.hip): they spend a good part of their steps there
-// where scores start above zero (64 sequences of K = 1024, T = 8: 2.5 times the
-// engine's time without, 0.7 with; long ones pay 3 to 7% for it in their other
-// steps).  Above kBoundListK states, which may not all find room on the lists,
-// they are the engine's.
+// Short sequences.  Up to K = 1024 and kMixT steps they take the bounded kernels
+// for scores of both signs (MIX in fv_bound.hip): they spend a good part of their
+// steps there where scores start above zero (64 sequences of K = 1024, in engine's
+// times, without and with: T = 8 2.5 and 0.7, T = 64 FLASH 1.2 and 0.9; others pay
+// 3 to 7% for it).  Above kBoundListK states, which may not all find room on the
+// lists, those up to kShortT steps are the engine's.
+constexpr int32_t kMixT = 64;
 constexpr int32_t kShortT = 32;
 constexpr int32_t kBoundListK = 2048;
 

@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-LONG = 40
+LONG = 70
 
 
 def _dev(x):
