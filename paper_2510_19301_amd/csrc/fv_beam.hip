@@ -25,8 +25,8 @@
 // they spawn, are left to the engine, which runs after this kernel.
 //
 // Measured against the engine: 64 sequences, K = 1024, T ~ U[200, 2000], B = 64,
-// P = 16: 91.4 -> 14.5 ms; 64 trajectories on 99,856 states, T ~ U[200, 2000],
-// B = 128, P = 16: 243 -> 18.0 ms (a step takes 8 us either way, half of it
+// P = 16: 91.4 -> 14.6 ms; 64 trajectories on 99,856 states, T ~ U[200, 2000],
+// B = 128, P = 16: 243 -> 14.6 ms (a step takes 8 and 6 us, half of it
 // the reads named above).
 #include <float.h>
 
