@@ -273,7 +273,7 @@ __device__ __forceinline__ void beam_keep(BeamBlk& s, int32_t B, uint32_t step, 
     // bins of about 1/80 of this beam's depth next
     inv = fminf(fmaxf(80.0f * inv / (float)(kb + 1), 1e-30f), 1e30f);
     if (cb == rem) return;
-    if (cb > kBeamRank) {
+    if (__builtin_expect(cb > kBeamRank, 0)) {
         unsigned long long w[2];
         static_assert(NV == 2, "entries per thread");
 #pragma unroll
